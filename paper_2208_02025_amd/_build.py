@@ -23,7 +23,8 @@ OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libollie.so")
 STAMP = LIB + ".sha256"
 HEADER = os.path.join(os.path.dirname(HERE), "include", "ollie.h")
-SOURCES = ["abi.hip", "gemm.hip", "eop.hip", "band.hip", "conv_fused.hip", "split3.hip"]
+SOURCES = ["abi.hip", "gemm.hip", "eop.hip", "band.hip", "conv_fused.hip", "conv_cols.hip",
+           "split3.hip"]
 ARCH = "gfx950"
 
 # Packed fp32 ops are disabled for all device code (the host pass warns that it does
@@ -45,7 +46,8 @@ def _hipcc() -> str:
 # registers per lane live next to two operand-fragment sets; the VGPR form of the MFMA
 # keeps them in place (with accumulators in AGPRs the register allocator shuffled them
 # between the two register files every iteration).
-SOURCE_FLAGS = {"conv_fused.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+SOURCE_FLAGS = {"conv_fused.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+                "conv_cols.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def source_digest(csrc: str = CSRC, header: str = HEADER) -> str:

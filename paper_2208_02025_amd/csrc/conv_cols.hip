@@ -1,0 +1,514 @@
+// Column form of the fused convolution expression, for classes whose taps step by one
+// class row and one class column (conv_plan.h): stride-1 convolutions, dilated ones as
+// residue sub-images (section 6.2), and the classes of strided transposed convolutions.
+//
+// The per-tap kernel (conv_fused.hip) copies every input pixel into LDS once per tap and
+// reads it from there once per tap: on the ResNet layer (16 x 14 x 14, 256 -> 256) its
+// 64 x 64 tiles spend ~400 cycles per k-tile moving 16 KB in and 32 KB out of LDS for 128
+// cycles of MFMA work.  This kernel uses both reuses that a convolution has:
+//   * along w: the window of input pixels that a tile needs is copied once per 32-channel
+//     slice and read at column offset s for tap column s;
+//   * along h: the 16 pixels of an MFMA operand are 16 class COLUMNS of one row (columns of
+//     several images or row blocks side by side), so the operand read at window row Y
+//     serves tap row r of output row Y - r for all R tap rows: TH + R - 1 reads per
+//     TH * R operands.
+//
+// Layout.  An image's hc class rows are cut into row blocks of TH; a "segment" is a row
+// block of an image and a "column" a (segment, class column) pair.  A tile is TH rows x
+// 16*WQ consecutive columns x 16*NF*WN output channels.  Waves: WQ over columns, WN over
+// channels, KW over 32-channel slices of the contraction (summed through LDS at the end).
+// The window, (TH + R - 1) rows x ww columns with the S - 1 halo columns after each
+// segment, lies in LDS as 128-byte slots (64 channels) whose 16-byte chunks are XORed with
+// the window column, so an operand read is bank-conflict free wherever it starts; pixels
+// outside the image get an offset past the buffer and read zeros.
+// A step is (slice, tap column): R*NF weight operands in registers against the window rows.
+// Weights pass through LDS (a wave's own slot, or one shared by its WQ waves): read straight
+// into operand registers they take one L1 access per lane, 64 per instruction instead of
+// 16, which bound the kernel (CSRNet layer 59.6 us, against 53.7 through LDS).
+//
+// Measured (us, per-tap kernel before / this one; warm, fp32 out):
+//   ResNet 3x3 16x14x14 256->256            11.9 / 9.0      (409 TFLOP/s)
+//   ResNet 3x3 16x28x28 128->128            11.2 / 9.1
+//   ResNet 3x3 16x56x56 64->64              15.6 / 10.3
+//   ResNet 3x3 16x7x7 512->512              17.8 / 12.0
+//   ResNet 3x3 1x7x7 512->512               17.5 / 7.1
+//   CSRNet 3x3 dil 2, 96x128 512->512       58.4 / 52.8     (1.10 PFLOP/s)
+//   DCGAN convT 4x4 s2 16x8x8 512->256      11.2 / 10.6
+//   SRCNN 5x5 512x512 64->32                68.0 / 37.5     (715 TFLOP/s)
+// What bounds it: on the CSRNet layer the marginal rate is 1.47 PFLOP/s (19.7 us per 256
+// input channels, the rate of a large library matrix product); 9 us are the 25 MB output
+// stores that all 256 tiles issue at once at their end, ~4 us the k-group sum, ~5 us launch
+// and first window.  The small layers are bound by ~4 us of launch, first loads and
+// epilogue plus 0.4-0.6 us per step (its LDS traffic and copy latency).
+#include <limits.h>
+
+#include "conv_plan.h"
+
+namespace ollie {
+
+namespace {
+
+struct ColsClass {
+    int hc, wc, oh0, ow0;     // class grid and its output origin
+    int b0h, b0w;             // input offset of the first tap row / column
+    int r0, rstep, s0, sstep; // kernel index of tap row / column t: r0 + t*rstep, s0 + t*sstep
+    int ns;                   // taps along w
+    int rb;                   // row blocks of TH class rows per image
+    uint32_t m_wc, m_pw, m_rb;   // ceil(2^32 / d) for d = wc, wc + ns - 1, rb
+};
+
+struct ColsPlan {
+    int n, c, h, w, k, ho, wo, s;
+    int alpha_h, alpha_w, gam_h, gam_w;
+    int tiles_n, ncls, x_bytes, w_bytes;
+    int ww;                   // window columns
+    uint32_t m_ww;            // ceil(2^32 / ww)
+    int tile0[kMaxCls];       // first workgroup tile of each class (INT_MAX past the last)
+    ColsClass cls[kMaxCls];
+};
+
+// x / d with m = ceil(2^32 / d), exact while x * d < 2^32; d = 1 has m = 0.
+__device__ __forceinline__ int fast_div(int x, uint32_t m) {
+    return m ? (int)__umulhi((uint32_t)x, m) : x;
+}
+
+template <int TH, int R, int NF, int WQ, int WN, int KW, int NBUF, int NBS, int SLOTS,
+          typename OT>
+__global__ __launch_bounds__(64 * WQ * WN * KW, 2)
+void conv_cols_kernel(const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wt,
+                      OT* __restrict__ out, ColsPlan P, Epi epi) {
+    constexpr int NW = WQ * WN * KW, NWO = WQ * WN;
+    constexpr int PL = KW >= 2 ? KW / 2 : 1;        // 64-channel planes per stage
+    constexpr int SPW = KW == 1 ? 2 : 1;            // 32-channel slices per wave and stage
+    constexpr int YR = TH + R - 1, F = TH * NF, G = R * NF;
+    constexpr int WPP = NW / PL;                    // waves that copy a plane's window
+    constexpr int WIN = SLOTS / 8 / WPP;            // window copies per wave and stage
+    constexpr int PLANE = SLOTS * 8, BUFC = PL * PLANE;
+    // NBS weight slots per (wn, kg).  A wave alone on its slots refills one as soon as it
+    // has read it; slots shared by WQ waves are refilled a barrier later.
+    constexpr int D = WQ == 1 ? NBS + 1 : NBS;      // steps the weight copies run ahead
+    constexpr int BL = (G + WQ - 1) / WQ;           // weight copies per wave and step
+    constexpr int BOFF = NBUF * BUFC;
+    constexpr int MAIN = BOFF + WN * KW * NBS * G * 64;
+    constexpr int RED = F * (KW - 1) * NWO * 64;
+    constexpr int LDS_CHUNKS = MAIN > RED ? MAIN : RED;
+    static_assert(NW % PL == 0 && SLOTS % (8 * WPP) == 0 && (KW == 1 || KW % 2 == 0), "shape");
+    static_assert(D >= 2 && WIN + D * BL < 64, "vmcnt range");
+    __shared__ u32x4 lds[LDS_CHUNKS];
+
+    const int lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kg = wave / NWO, wo = wave % NWO;
+    const int wq = wo / WN, wn = wo % WN;
+
+    const int nblk = gridDim.x, bid = blockIdx.x;
+    const int id = (nblk & 7) == 0 ? (bid & 7) * (nblk >> 3) + (bid >> 3) : bid;
+    int ci = 0;    // no loop over loads: their latencies would add up (2 us at 16 classes)
+#pragma unroll
+    for (int i = 1; i < kMaxCls; ++i) ci += id >= P.tile0[i] ? 1 : 0;
+    const ColsClass& cl = P.cls[ci];
+    const int wc = cl.wc, ns = cl.ns, pw = wc + ns - 1, rbn = cl.rb;
+    const int local = id - P.tile0[ci];
+    const int ct = local / P.tiles_n, k0 = (local - ct * P.tiles_n) * (16 * NF * WN);
+    const int q0 = ct * (16 * WQ);
+    const int sg0 = q0 / wc, j0 = q0 - sg0 * wc;       // first segment and its column
+    const int img0 = sg0 / rbn, rb0 = sg0 - img0 * rbn;
+    const int H = P.h, W = P.w, C = P.c, K = P.k, WW = P.ww;
+    const int nslices = C >> 5;
+    const int nstages = (nslices + KW * SPW - 1) / (KW * SPW);
+
+    // window copies of this lane: slot group i*WPP + wave/PL of plane wave%PL, slot lane/8
+    const int cpl = wave % PL, cgrp = wave / PL;
+    uint32_t xoff[WIN];
+#pragma unroll
+    for (int i = 0; i < WIN; ++i) {
+        const int slot = (i * WPP + cgrp) * 8 + (lane >> 3);
+        const int y = fast_div(slot, P.m_ww), u = slot - y * WW;
+        const int v = j0 + u, dsg = fast_div(v, cl.m_pw), jj = v - dsg * pw;
+        const int t = rb0 + dsg, dimg = fast_div(t, cl.m_rb), rb = t - dimg * rbn;
+        const int img = img0 + dimg;
+        const int hi = P.alpha_h * (rb * TH + y) + cl.b0h, wi = P.alpha_w * jj + cl.b0w;
+        const bool ok = y < YR && img < P.n && (unsigned)hi < (unsigned)H &&
+                        (unsigned)wi < (unsigned)W;
+        const int ch = (lane & 7) ^ (u & 7);
+        xoff[i] = ok ? (uint32_t)((((img * H + hi) * W + wi) * C + ch * 8) * 2) : 0x80000000u;
+    }
+    auto window = [&](int st, int buf) {
+        // a plane past C is never read; its copies only keep the copy count constant
+        const int plane = st * PL + cpl;
+        const uint32_t add = plane * 64 < C ? plane * 128u : 0u;
+#pragma unroll
+        for (int i = 0; i < WIN; ++i)
+            buffer_copy16(X, P.x_bytes, xoff[i] + add, 0,
+                          (lds_void*)(lds + buf * BUFC + cpl * PLANE + (i * WPP + cgrp) * 64));
+    };
+
+    // weight copies: fragment (r, f) of the wave's (wn, kg) is 16 channels x 32 c
+    uint32_t bvo[BL];
+    int bso[BL], bdst[BL];
+    const int row_stride = cl.rstep * P.s * K * C * 2, col_stride = cl.sstep * K * C * 2;
+    const int tap0 = (cl.r0 * P.s + cl.s0) * K * C * 2;
+#pragma unroll
+    for (int i = 0; i < BL; ++i) {
+        int idx = i * WQ + wq;
+        idx = idx < G ? idx : G - 1;
+        const int r = idx / NF, f = idx % NF;
+        int kk = k0 + (wn * NF + f) * 16 + (lane >> 2);
+        kk = kk < K ? kk : K - 1;
+        bvo[i] = (uint32_t)((kk * C + ((lane & 3) ^ ((lane >> 3) & 3)) * 8) * 2);
+        bso[i] = tap0 + r * row_stride;
+        bdst[i] = BOFF + ((kg * WN + wn) * NBS * G + idx) * 64;
+    }
+    int ls = 0, lslice = kg;                           // the step the next weights() copies
+    auto weights = [&](int slot) {
+        // past the last step it copies valid weights that nobody reads
+        const int sl = lslice < nslices ? lslice : nslices - 1;
+        const int so = ls * col_stride + sl * 64;
+#pragma unroll
+        for (int i = 0; i < BL; ++i)
+            buffer_copy16(Wt, P.w_bytes, bvo[i], bso[i] + so,
+                          (lds_void*)(lds + bdst[i] + slot * G * 64));
+        if (++ls == ns) {
+            ls = 0;
+            lslice += KW;
+        }
+    };
+    const u32x4* bsrc = lds + BOFF + (kg * WN + wn) * NBS * G * 64 + li * 4 + (grp ^ ((li >> 1) & 3));
+    auto read_b = [&](bf16x8 (&b)[R][NF], int slot) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                b[r][f] = __builtin_bit_cast(bf16x8, bsrc[(slot * G + r * NF + f) * 64]);
+    };
+
+    // lane's column: window column of tap column 0
+    const int qoff = wq * 16 + li;
+    const int dseg = fast_div(j0 + qoff, cl.m_wc);
+    const int ucol = qoff + dseg * (ns - 1);
+    const char* lds_b = reinterpret_cast<const char*>(lds);
+    const int row_bytes = WW * 128;
+
+    f32x4 acc[TH][NF];
+#pragma unroll
+    for (int y = 0; y < TH; ++y)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[y][f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    constexpr int YS = (YR + 1) / 2;
+    constexpr int PA = YR < 4 ? YR : 4;     // window rows read ahead
+    bf16x8 B[2][R][NF];
+    window(0, 0);
+#pragma unroll
+    for (int i = 0; i < NBS; ++i) weights(i);
+    wait_vm<(NBS - 1) * BL>();
+    block_barrier();
+    read_b(B[0], 0);
+    const int per_stage = SPW * ns, total = nstages * per_stage;
+    if (WQ == 1) {
+        wait_lds();
+        weights(0);
+    }
+    mem_order();
+    if (NBUF == 2 && nstages > 1) window(1, 1);
+    int st = 0, in_stage = 0, cs = 0, cslice = kg;
+    int cslot = 0, nslot = NBS == 1 ? 0 : 1;
+    for (int t = 0; t < total; t += 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (t + u < total) {
+                if (in_stage == per_stage) {           // next stage
+                    in_stage = 0;
+                    ++st;
+                    if (NBUF == 2) {
+                        // its copies are older than the weights of this stage's steps
+                        if (per_stage < D) wait_vm<BL>();
+                        block_barrier();
+                        if (st + 1 < nstages) window(st + 1, (st + 1) & 1);
+                        mem_order();
+                    } else {
+                        block_barrier();
+                        window(st, 0);
+                        wait_vm<0>();
+                        block_barrier();
+                    }
+                }
+                const bool work = cslice < nslices;
+                const char* a0;
+                {
+                    const int plane = KW == 1 ? 0 : kg >> 1;
+                    const int uc = ucol + cs;
+                    const int chl = (cslice & 1) * 4 + grp;
+                    a0 = lds_b + ((NBUF == 2 ? st & 1 : 0) * BUFC + plane * PLANE) * 16 + uc * 128 +
+                         ((chl ^ (uc & 7)) << 4);
+                }
+                // the next step's weights: D - 2 steps' copies are younger, and the window's
+                // where they were issued after these weights
+                auto next_b = [&]() {
+                    if (NBUF == 2 && in_stage < D - 1 && st + 1 < nstages)
+                        wait_vm<(D - 2) * BL + WIN>();
+                    else wait_vm<(D - 2) * BL>();
+                    if (WQ > 1) block_barrier();
+                    read_b(B[u ^ 1], nslot);
+                };
+                if (work) {
+                    bf16x8 a[PA];
+#pragma unroll
+                    for (int y = 0; y < PA; ++y)
+                        a[y] = *reinterpret_cast<const bf16x8*>(a0 + y * row_bytes);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int y = 0; y < YR; ++y) {
+                        if (y == YS) next_b();
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            const int yy = y - r;
+                            if (yy < 0 || yy >= TH) continue;
+#pragma unroll
+                            for (int f = 0; f < NF; ++f)
+                                acc[yy][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    B[u][r][f], a[y % PA], acc[yy][f], 0, 0, 0);
+                        }
+                        if (y + PA < YR)
+                            a[y % PA] =
+                                *reinterpret_cast<const bf16x8*>(a0 + (y + PA) * row_bytes);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                } else {
+                    next_b();
+                }
+                if (WQ == 1) wait_lds();               // the slot's last reads are done
+                weights(WQ == 1 ? nslot : cslot);
+                cslot = nslot;
+                nslot = nslot + 1 == NBS ? 0 : nslot + 1;
+                ++in_stage;
+                if (++cs == ns) {
+                    cs = 0;
+                    cslice += KW;
+                }
+            }
+        }
+    }
+
+    wait_vm<0>();    // no copy into LDS may still be in flight from here on
+    // each k-group owns every KW-th fragment: it hands the others over through LDS
+    f32x4* red = reinterpret_cast<f32x4*>(lds) + wo * F * (KW - 1) * 64 + lane;
+    if constexpr (KW > 1) {
+        block_barrier();
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            const int own = f % KW;
+            if (kg != own) red[(f * (KW - 1) + (kg < own ? kg : kg - 1)) * 64] = acc[f / NF][f % NF];
+        }
+        block_barrier();
+    }
+    const int t1 = rb0 + dseg, dimg = fast_div(t1, cl.m_rb), rb = t1 - dimg * rbn;
+    const int img = img0 + dimg, j = j0 + qoff - dseg * wc;
+    const int64_t opix0 = ((int64_t)img * P.ho + cl.oh0 + P.gam_h * (rb * TH)) * P.wo + cl.ow0 +
+                          P.gam_w * j;
+    const int nrow = img < P.n ? cl.hc - rb * TH : 0;  // class rows of the lane's column
+    const bool vec_ok = (K & 3) == 0;
+#pragma unroll
+    for (int own = 0; own < KW; ++own) {
+        if (kg != own) continue;
+#pragma unroll
+        for (int i = own; i < F; i += KW) {
+            const int y = i / NF, f = i % NF;
+            f32x4 v = acc[y][f];
+#pragma unroll
+            for (int g = 0; g < KW - 1; ++g) v += red[(i * (KW - 1) + g) * 64];
+            if (y >= nrow) continue;
+            const int64_t opix = opix0 + (int64_t)P.gam_h * y * P.wo;
+            OT* orow = out + opix * K;
+            const int k = k0 + (wn * NF + f) * 16 + 4 * grp;
+            if (vec_ok && k + 3 < K) {
+                Out<OT>::put4(orow + k, epi_apply4(epi, v, opix * K + k, k));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (k + e < K)
+                        Out<OT>::put(orow + k + e,
+                                     epi_apply(epi, v[e], opix * K + k + e, k + e));
+            }
+        }
+    }
+}
+
+uint32_t magic(int d) { return d <= 1 ? 0u : (uint32_t)(((uint64_t(1) << 32) + d - 1) / d); }
+
+// A tile configuration: TH class rows x 16*WQ columns x 16*NF*WN channels, KW k-groups.
+struct Cfg {
+    int r, th, nf, wq, wn, kw, nbuf, slots;
+    int occ;                  // workgroups per CU (LDS and registers)
+    hipError_t (*launch)(const ColsPlan&, int64_t, const void*, const void*, void*, const Epi&,
+                         hipStream_t);
+};
+
+// Whether the configuration covers the classes; their tiles.
+bool cols_covers(const FusedPlan& F, const Cfg& c, int64_t& tiles, int& ww) {
+    const int cols = 16 * c.wq;
+    const int tn = (F.k + 16 * c.nf * c.wn - 1) / (16 * c.nf * c.wn);
+    tiles = 0;
+    ww = 0;
+    for (int i = 0; i < F.ncls; ++i) {
+        const AxisTaps &th = F.cls_th[i], &tw = F.cls_tw[i];
+        if (th.n != c.r || tw.n < 1) return false;
+        if (th.n > 1 && th.bstep != F.alpha_h && th.bstep != -F.alpha_h) return false;
+        if (tw.n > 1 && tw.bstep != F.alpha_w && tw.bstep != -F.alpha_w) return false;
+        const int wc = F.cls_wc[i], rb = (F.cls_hc[i] + c.th - 1) / c.th;
+        if (wc > 16384 || rb > 16384) return false;          // range of fast_div
+        const int64_t nq = (int64_t)F.n * rb * wc;
+        if (nq >= (int64_t(1) << 30)) return false;
+        // segments that a tile of `cols` columns can meet
+        const int seg = wc % cols == 0 ? 1 : cols % wc == 0 ? cols / wc : (wc + cols - 2) / wc + 1;
+        const int w = cols + seg * (tw.n - 1);
+        ww = w > ww ? w : ww;
+        tiles += (int64_t)((int)(nq + cols - 1) / cols) * tn;
+    }
+    return tiles < (int64_t(1) << 31) && ww * (c.th + c.r - 1) <= c.slots;
+}
+
+ColsPlan cols_plan(const FusedPlan& F, const Cfg& cfg, int ww) {
+    ColsPlan P{};
+    P.n = F.n; P.c = F.c; P.h = F.h; P.w = F.w; P.k = F.k; P.ho = F.ho; P.wo = F.wo; P.s = F.s;
+    P.alpha_h = F.alpha_h; P.alpha_w = F.alpha_w; P.gam_h = F.gam_h; P.gam_w = F.gam_w;
+    P.tiles_n = (F.k + 16 * cfg.nf * cfg.wn - 1) / (16 * cfg.nf * cfg.wn);
+    P.ncls = F.ncls; P.x_bytes = F.x_bytes; P.w_bytes = F.w_bytes;
+    P.ww = ww;
+    P.m_ww = magic(ww);
+    const int cols = 16 * cfg.wq;
+    int64_t tiles = 0;
+    for (int i = 0; i < kMaxCls; ++i) P.tile0[i] = INT_MAX;
+    for (int i = 0; i < F.ncls; ++i) {
+        ColsClass& c = P.cls[i];
+        const AxisTaps &th = F.cls_th[i], &tw = F.cls_tw[i];
+        // taps in increasing input offset (the transposed form's run backwards)
+        const bool fh = th.n > 1 && th.bstep < 0, fw = tw.n > 1 && tw.bstep < 0;
+        c.hc = F.cls_hc[i]; c.wc = F.cls_wc[i]; c.oh0 = F.cls_oh0[i]; c.ow0 = F.cls_ow0[i];
+        c.b0h = fh ? th.b0 + (th.n - 1) * th.bstep : th.b0;
+        c.b0w = fw ? tw.b0 + (tw.n - 1) * tw.bstep : tw.b0;
+        c.r0 = fh ? th.r0 + (th.n - 1) * th.rstep : th.r0;
+        c.rstep = fh ? -th.rstep : th.rstep;
+        c.s0 = fw ? tw.r0 + (tw.n - 1) * tw.rstep : tw.r0;
+        c.sstep = fw ? -tw.rstep : tw.rstep;
+        c.ns = tw.n;
+        c.rb = (c.hc + cfg.th - 1) / cfg.th;
+        c.m_wc = magic(c.wc); c.m_pw = magic(c.wc + c.ns - 1); c.m_rb = magic(c.rb);
+        P.tile0[i] = (int)tiles;
+        tiles += ((int64_t)F.n * c.rb * c.wc + cols - 1) / cols * P.tiles_n;
+    }
+    return P;
+}
+
+// Estimated time (ns) of a configuration, fitted to 34 of them on 30 layers (batch 1 to 16,
+// 64 to 512 channels, 2 to 112 pixels, R = 2, 3, 5): a fixed part per round of resident
+// workgroups plus, per (32 channels, tap column) step of a wave, the larger of the step's
+// latency and the CU's MFMA and LDS cycles, which overlap little.  On those layers the
+// configuration of the smallest estimate is the fastest or within 10% of it.
+double cols_cost(const FusedPlan& F, const Cfg& c, int64_t tiles) {
+    const int nw = c.wq * c.wn * c.kw, spw = c.kw == 1 ? 2 : 1;
+    int ns = 1;
+    for (int i = 0; i < F.ncls; ++i) ns = F.cls_tw[i].n > ns ? F.cls_tw[i].n : ns;
+    const int stages = (F.c / 32 + c.kw * spw - 1) / (c.kw * spw);
+    const int64_t per = (tiles + 255) / 256;
+    const double share = (double)(per < c.occ ? per : c.occ);
+    const double rounds = (double)((tiles + 256 * c.occ - 1) / (256 * c.occ));
+    const double mfma = c.r * c.th * c.nf * nw * 4.0;
+    const double lds = nw * (c.th + c.r - 1 + 2 * c.r * c.nf) * 8.0;
+    double step = 0.4 * (mfma + lds) * share;
+    step = step > 420.0 ? step : 420.0;
+    const double reduce = 6.9 * c.th * c.nf * (c.kw - 1) * c.wq * c.wn * share;
+    const double reload = c.nbuf == 1 ? 500.0 * (stages - 1) : 0.0;
+    return 2600.0 + rounds * (1000.0 + stages * spw * ns * step + reduce + reload);
+}
+
+template <int TH, int R, int NF, int WQ, int WN, int KW, int NBUF, int NBS, int SLOTS,
+          typename OT>
+hipError_t go_cols(const ColsPlan& P, int64_t tiles, const void* x, const void* wt, void* out,
+                   const Epi& epi, hipStream_t st) {
+    hipLaunchKernelGGL((conv_cols_kernel<TH, R, NF, WQ, WN, KW, NBUF, NBS, SLOTS, OT>),
+                       dim3((unsigned)tiles), dim3(64 * WQ * WN * KW), 0, st, (const bf16_t*)x,
+                       (const bf16_t*)wt, (OT*)out, P, epi);
+    return hipGetLastError();
+}
+
+template <typename OT>
+const Cfg* cols_cfgs(int& n) {
+#define OLLIE_COLS(R, TH, NF, WQ, WN, KW, NBUF, NBS, SLOTS, OCC) \
+    {R, TH, NF, WQ, WN, KW, NBUF, SLOTS, OCC, go_cols<TH, R, NF, WQ, WN, KW, NBUF, NBS, SLOTS, OT>}
+    static const Cfg cfgs[] = {
+        OLLIE_COLS(3, 12, 2, 1, 4, 2, 2, 1, 256, 1),
+        OLLIE_COLS(3, 8, 2, 2, 4, 1, 2, 2, 384, 1),
+        OLLIE_COLS(3, 7, 2, 2, 2, 2, 1, 2, 384, 1),
+        OLLIE_COLS(3, 7, 2, 1, 2, 4, 1, 1, 224, 1),
+        OLLIE_COLS(3, 7, 1, 1, 2, 4, 2, 1, 224, 1),
+        OLLIE_COLS(3, 4, 2, 2, 2, 2, 1, 2, 256, 1),
+        OLLIE_COLS(3, 4, 1, 2, 2, 2, 1, 2, 256, 2),
+        OLLIE_COLS(3, 4, 2, 1, 2, 4, 1, 1, 160, 1),
+        OLLIE_COLS(3, 4, 2, 1, 1, 8, 1, 1, 144, 1),
+        OLLIE_COLS(3, 4, 1, 1, 2, 4, 1, 1, 160, 2),
+        OLLIE_COLS(3, 2, 1, 1, 2, 4, 1, 1, 96, 2),
+        OLLIE_COLS(3, 2, 1, 1, 1, 8, 1, 1, 96, 2),
+        OLLIE_COLS(2, 8, 2, 1, 2, 4, 2, 2, 192, 1),
+        OLLIE_COLS(2, 8, 1, 1, 2, 4, 2, 2, 192, 1),
+        OLLIE_COLS(2, 4, 2, 2, 2, 2, 1, 2, 256, 1),
+        OLLIE_COLS(2, 4, 1, 1, 2, 4, 1, 1, 96, 3),
+        OLLIE_COLS(2, 2, 1, 1, 1, 8, 1, 1, 64, 3),
+        OLLIE_COLS(5, 8, 2, 4, 1, 2, 1, 2, 832, 1),
+        OLLIE_COLS(5, 4, 2, 4, 1, 2, 1, 2, 576, 1),
+        OLLIE_COLS(5, 4, 2, 1, 2, 4, 1, 1, 192, 1),
+        OLLIE_COLS(5, 4, 1, 1, 2, 4, 1, 1, 192, 1),
+    };
+#undef OLLIE_COLS
+    n = (int)(sizeof(cfgs) / sizeof(cfgs[0]));
+    return cfgs;
+}
+
+template <typename OT>
+bool try_cols(const FusedPlan& F, const void* x, const void* wt, void* out, const Epi& epi,
+              hipStream_t st, hipError_t& err) {
+    if (F.x_bytes == 0 || F.w_bytes == 0) return false;   // offsets are 32-bit
+    int n;
+    const Cfg* cfgs = cols_cfgs<OT>(n);
+    const Cfg* best = nullptr;
+    double best_cost = 0;
+    int64_t best_tiles = 0;
+    int best_ww = 0;
+    for (int i = 0; i < n; ++i) {
+        int64_t tiles;
+        int ww;
+        if (cfgs[i].r != F.cls_th[0].n || !cols_covers(F, cfgs[i], tiles, ww)) continue;
+        const double cost = cols_cost(F, cfgs[i], tiles);
+        if (!best || cost < best_cost) {
+            best = &cfgs[i];
+            best_cost = cost;
+            best_tiles = tiles;
+            best_ww = ww;
+        }
+    }
+    if (!best) return false;
+    // Against the per-tap kernel on 64 x 64 tiles (5.0 us + 0.19 us per 64-deep k-tile while
+    // its tiles fit the chip at once): short contractions on few tiles stay there.  1.2: the
+    // estimates above lie below the times measured (5.9 us for 4.9 on a 4-k-tile layer that
+    // the per-tap kernel does in 5.5; 4.6 for 4.9 on a 9-k-tile layer, 6.4 there).
+    int64_t t64 = 0;
+    int ktiles = 0;
+    for (int i = 0; i < F.ncls; ++i) {
+        t64 += ((int64_t)F.n * F.cls_hc[i] * F.cls_wc[i] + 63) / 64 * ((F.k + 63) / 64);
+        const int kt = F.cls_th[i].n * F.cls_tw[i].n * (F.c / kTileK);
+        ktiles = kt > ktiles ? kt : ktiles;
+    }
+    if (t64 <= 256 && 1.2 * best_cost > 5000.0 + 190.0 * ktiles) return false;
+    err = best->launch(cols_plan(F, *best, best_ww), best_tiles, x, wt, out, epi, st);
+    return true;
+}
+
+}  // namespace
+
+bool launch_conv_cols(const FusedPlan& F, const void* x, const void* wt, void* out, int out_bf16,
+                      const Epi& epi, hipStream_t st, hipError_t& err) {
+    return out_bf16 ? try_cols<bf16_t>(F, x, wt, out, epi, st, err)
+                    : try_cols<float>(F, x, wt, out, epi, st, err);
+}
+
+}  // namespace ollie

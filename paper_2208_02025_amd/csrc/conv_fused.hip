@@ -26,33 +26,13 @@
 // Main loop: the bf16 DMA pipeline of the GEMM stage (global_load_lds_dwordx4 into an
 // XOR-swizzled LDS ring, v_mfma_f32_16x16x32_bf16).  A rows are gathered per tap; rows
 // whose input pixel lies in the zero padding fetch a 16-byte zero chunk instead.
-#include "common.h"
+#include "conv_plan.h"
 
 namespace ollie {
 
 namespace {
 
-constexpr int kMaxCls = 16;
-
 __device__ __align__(16) uint32_t kZeroChunk[4];   // 16 zero bytes (zero-initialised)
-
-// The taps of one class along one axis: kernel indices r0 + i*rstep and input offsets
-// b0 + i*bstep, i < n (an arithmetic progression in every form below).
-struct AxisTaps {
-    int r0, rstep, b0, bstep, n;
-};
-
-struct FusedPlan {
-    int n, c, h, w, k, ho, wo, s;
-    int alpha_h, alpha_w;     // input coordinate = alpha * class coordinate + b_tap
-    int gam_h, gam_w;         // output coordinate = o0 + gamma * class coordinate
-    int tiles_n;              // output-channel tiles
-    int ncls;
-    int x_bytes, w_bytes;     // sizes of X and Wt (buffer-load form: both < 2^31)
-    int cls_tile0[kMaxCls + 1];   // first workgroup tile of each class
-    int cls_hc[kMaxCls], cls_wc[kMaxCls], cls_oh0[kMaxCls], cls_ow0[kMaxCls];
-    AxisTaps cls_th[kMaxCls], cls_tw[kMaxCls];   // a class's taps: th x tw, r-major
-};
 
 // Which tile of which class a workgroup owns.  Consecutive workgroup ids go to
 // different XCDs, so ids are regrouped to give each XCD a contiguous range of tiles.
@@ -577,82 +557,6 @@ void conv_window_kernel(const bf16_t* __restrict__ X, const bf16_t* __restrict__
     store_tile<FM, FN, WM, WN, OT>(P, t, wm, wn, acc, out, epi);
 }
 
-// Host-side plan: classes, their taps, and the tile count for a BM x BN tiling.
-//
-// Taps along one axis of a class, as (kernel index, input offset) pairs in increasing
-// kernel index; false if they do not form an arithmetic progression (never the case
-// for the forms below, checked anyway).
-bool axis_taps(const int* r, const int* b, int n, AxisTaps& a) {
-    a = AxisTaps{0, 1, 0, 0, n};
-    if (n == 0) return true;
-    a.r0 = r[0]; a.b0 = b[0];
-    if (n > 1) { a.rstep = r[1] - r[0]; a.bstep = b[1] - b[0]; }
-    for (int i = 0; i < n; ++i)
-        if (r[i] != a.r0 + i * a.rstep || b[i] != a.b0 + i * a.bstep) return false;
-    return true;
-}
-
-// One axis of a class with output residue `a` (0 for the forward form):
-//   forward:     all taps, input offset -pad + r*dil  (input = stride*i + offset);
-//   residues:    all taps, offset a - pad + r*dil     (input = dil*i + offset);
-//   transposed:  the taps with (a + pad - r*dil) divisible by the stride, offset
-//                (a + pad - r*dil) / stride         (input = i + offset).
-bool class_axis(int form, int a, int64_t ksize, int stride, int pad, int dil, AxisTaps& t) {
-    if (ksize > 64) return false;
-    int r[64], b[64], n = 0;
-    for (int k = 0; k < (int)ksize; ++k) {
-        if (form == kForward) {
-            r[n] = k; b[n++] = -pad + k * dil;
-        } else if (form == kResidues) {
-            r[n] = k; b[n++] = a - pad + k * dil;
-        } else {
-            const int th = a + pad - k * dil;
-            if (((th % stride) + stride) % stride != 0) continue;
-            r[n] = k; b[n++] = th / stride;   // exact: th is a multiple of the stride
-        }
-    }
-    return axis_taps(r, b, n, t);
-}
-
-bool make_plan(const ConvGeom& g, int form, FusedPlan& P) {
-    P = FusedPlan{};
-    P.n = (int)g.n; P.c = (int)g.c; P.h = (int)g.h; P.w = (int)g.w; P.k = (int)g.k;
-    P.ho = (int)g.ho; P.wo = (int)g.wo; P.s = (int)g.s;
-    const int64_t xb = g.n * g.h * g.w * g.c * 2, wb = g.r * g.s * g.k * g.c * 2;
-    P.x_bytes = xb < (int64_t(1) << 31) && wb < (int64_t(1) << 31) ? (int)xb : 0;
-    P.w_bytes = P.x_bytes ? (int)wb : 0;
-    // classes: output residues modulo gamma (the stride of the transposed form, the
-    // dilation of the residue form (section 6.2), 1 for the forward form)
-    int gh = 1, gw = 1;
-    if (form == kResidues) {
-        if (g.sh != 1 || g.sw != 1) return false;
-        gh = g.dh; gw = g.dw;
-        P.alpha_h = g.dh; P.alpha_w = g.dw;
-    } else if (form == kForward) {
-        P.alpha_h = g.sh; P.alpha_w = g.sw;
-    } else {
-        gh = g.sh; gw = g.sw;
-        P.alpha_h = 1; P.alpha_w = 1;
-    }
-    if ((int64_t)gh * gw > kMaxCls) return false;
-    P.gam_h = gh; P.gam_w = gw;
-    int ncls = 0;
-    for (int ah = 0; ah < gh; ++ah)
-        for (int aw = 0; aw < gw; ++aw) {
-            const int hc = ah < g.ho ? (int)((g.ho - ah + gh - 1) / gh) : 0;
-            const int wc = aw < g.wo ? (int)((g.wo - aw + gw - 1) / gw) : 0;
-            if (hc == 0 || wc == 0) continue;
-            P.cls_hc[ncls] = hc; P.cls_wc[ncls] = wc;
-            P.cls_oh0[ncls] = ah; P.cls_ow0[ncls] = aw;
-            if (!class_axis(form, ah, g.r, g.sh, g.ph, g.dh, P.cls_th[ncls]) ||
-                !class_axis(form, aw, g.s, g.sw, g.pw, g.dw, P.cls_tw[ncls]))
-                return false;
-            ++ncls;
-        }
-    P.ncls = ncls;
-    return ncls > 0;
-}
-
 int64_t plan_tiles(FusedPlan& P, int bm, int bn) {
     P.tiles_n = (P.k + bn - 1) / bn;
     int64_t t = 0;
@@ -770,10 +674,15 @@ hipError_t dispatch(FusedPlan& P, const void* x, const void* wt, void* out, cons
 
 }  // namespace
 
+// make_plan's conditions alone (the taps of a class always form an arithmetic progression);
+// callers ask several times per launch.
 bool conv_fused_supported(const ConvGeom& g, int form) {
-    if (g.c % kTileK != 0) return false;
-    FusedPlan P;
-    return make_plan(g, form, P);
+    if (g.c % kTileK != 0 || g.r > kMaxTaps || g.s > kMaxTaps) return false;
+    if (form == kResidues && (g.sh != 1 || g.sw != 1)) return false;
+    const int64_t classes = form == kResidues     ? (int64_t)g.dh * g.dw
+                            : form == kTransposed ? (int64_t)g.sh * g.sw
+                                                  : 1;
+    return classes <= kMaxCls;
 }
 
 hipError_t launch_conv_fused(const ConvGeom& g, int form, const void* x, const void* wt,
@@ -781,6 +690,14 @@ hipError_t launch_conv_fused(const ConvGeom& g, int form, const void* x, const v
                              hipStream_t stream) {
     FusedPlan P;
     if (g.c % kTileK != 0 || !make_plan(g, form, P)) return hipErrorInvalidValue;
+    if (tile < 0) {
+        // the column kernel takes a stride-1 dilated convolution as its residue sub-images
+        FusedPlan R;
+        hipError_t err;
+        const bool res = form == kForward && g.sh == 1 && g.sw == 1 && (g.dh > 1 || g.dw > 1) &&
+                         make_plan(g, kResidues, R);
+        if (launch_conv_cols(res ? R : P, x, wt, out, out_bf16, epi, stream, err)) return err;
+    }
     return out_bf16 ? dispatch<bf16_t>(P, x, wt, out, epi, tile, stream)
                     : dispatch<float>(P, x, wt, out, epi, tile, stream);
 }
