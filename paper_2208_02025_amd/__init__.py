@@ -15,6 +15,7 @@ Layouts (contiguous):
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -167,11 +168,18 @@ def _gpu(t: torch.Tensor, name: str):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(dev) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+# Raw handle of the current stream of a device index.  torch.cuda.current_stream builds a
+# Stream object first, 1 us of a call that launches in 3.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(dev) -> int:
+    if _raw_stream is None or dev.index is None:
+        return torch.cuda.current_stream(dev).cuda_stream
+    return _raw_stream(dev.index)
 
 
 def conv_desc(x_shape, wt_shape, stride=1, padding=0, dilation=1, output_padding=0,
@@ -213,6 +221,32 @@ def conv_epilogue(bias=None, residual=None, relu=False):
                         F32 if residual is None else _dtype_code(residual.dtype), int(bool(relu)))
 
 
+# What a call derives from its sizes and options alone, kept for the last calls' sizes: a
+# pass over a network repeats them, and building the descriptors and asking the library for
+# sizes took about half of a call's host time.  Keyed by values (typed, so that an argument
+# of a type that is refused stays refused); refusals raise and are not kept.
+_PLANS = 1024
+
+
+@functools.lru_cache(maxsize=_PLANS, typed=True)
+def _conv_plan(entry: str, transposed: bool, x_shape, wt_shape, dtype, stride, padding, dilation,
+               output_padding, out_dtype, flags: int):
+    """(descriptor reference, output shape, k, workspace bytes, entry point, its _ex form)"""
+    desc = conv_desc(x_shape, wt_shape, stride, padding, dilation, output_padding, dtype,
+                     out_dtype)
+    ho, wo = conv_out_hw(desc, transposed)
+    lib = load_library()
+    return (ctypes.byref(desc), (desc.n, ho, wo, desc.k), desc.k,
+            conv_workspace_bytes(desc, transposed, flags), getattr(lib, entry),
+            getattr(lib, "ollie_" + entry + "_ex"))
+
+
+def _key(v):
+    """A size option as a plan key: its plain integer values (a list, an array or a tensor is
+    never kept)."""
+    return v if isinstance(v, int) else (int(v[0]), int(v[1]))
+
+
 def _conv(entry: str, transposed: bool, x, wt, stride, padding, dilation, output_padding,
           out_dtype, y_bf16, out, ws, fuse=False, bias=None, residual=None, relu=False,
           extra_flags=0):
@@ -220,34 +254,32 @@ def _conv(entry: str, transposed: bool, x, wt, stride, padding, dilation, output
     _gpu(wt, "wt")
     if x.dtype != wt.dtype:
         raise ValueError("x and wt must have the same dtype")
-    desc = conv_desc(tuple(x.shape), tuple(wt.shape), stride, padding, dilation, output_padding,
-                     x.dtype, out_dtype)
     flags = (Y_BF16 if y_bf16 else 0) | (FUSE_EPILOGUE if fuse else 0) | extra_flags
-    ho, wo = conv_out_hw(desc, transposed)
+    desc, shape, k, need, fn, fn_ex = _conv_plan(
+        entry, transposed, x.shape, wt.shape, x.dtype, _key(stride), _key(padding),
+        _key(dilation), _key(output_padding), out_dtype, flags)
     if out is None:
-        out = torch.empty((desc.n, ho, wo, desc.k), dtype=out_dtype, device=x.device)
+        out = torch.empty(shape, dtype=out_dtype, device=x.device)
     else:
         _gpu(out, "out")
-        if tuple(out.shape) != (desc.n, ho, wo, desc.k) or out.dtype != out_dtype:
+        if tuple(out.shape) != shape or out.dtype != out_dtype:
             raise ValueError("out has the wrong shape or dtype")
-    need = conv_workspace_bytes(desc, transposed, flags)
     if ws is None and need:
         ws = torch.empty(need, dtype=torch.uint8, device=x.device)
     ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
     epi = conv_epilogue(bias, residual, relu)
-    if bias is not None and tuple(bias.shape) != (desc.k,):
-        raise ValueError(f"bias must have shape ({desc.k},)")
-    if residual is not None and tuple(residual.shape) != (desc.n, ho, wo, desc.k):
+    if bias is not None and tuple(bias.shape) != (k,):
+        raise ValueError(f"bias must have shape ({k},)")
+    if residual is not None and tuple(residual.shape) != shape:
         raise ValueError("residual must have the shape of out")
-    lib = load_library()
     if epi is None:
-        st = getattr(lib, entry)(ctypes.byref(desc), _ptr(x), _ptr(wt), _ptr(out), _ptr(ws),
-                                 ws_bytes, flags, _stream(x.device))
+        st = fn(desc, x.data_ptr(), wt.data_ptr(), out.data_ptr(), _ptr(ws), ws_bytes, flags,
+                _stream(x.device))
     else:
-        entry = "ollie_" + entry + "_ex"
-        st = getattr(lib, entry)(ctypes.byref(desc), _ptr(x), _ptr(wt), _ptr(out), _ptr(ws),
-                                 ws_bytes, flags, ctypes.byref(epi), _stream(x.device))
-    _check(st, entry)
+        st = fn_ex(desc, x.data_ptr(), wt.data_ptr(), out.data_ptr(), _ptr(ws), ws_bytes, flags,
+                   ctypes.byref(epi), _stream(x.device))
+    if st != OK:
+        _check(st, entry if epi is None else "ollie_" + entry + "_ex")
     return out
 
 
@@ -323,6 +355,14 @@ def band_workspace_bytes(desc: BandDesc, flags: int) -> int:
     return int(load_library().ollie_band_workspace_bytes(ctypes.byref(desc), flags))
 
 
+@functools.lru_cache(maxsize=_PLANS, typed=True)
+def _band_plan(q_shape, w, dilation, scale, out_dtype, flags: int):
+    """(descriptor reference, output shape, shape of S, workspace bytes, entry point)"""
+    desc = band_desc(q_shape, w, dilation, scale, out_dtype)
+    return (ctypes.byref(desc), tuple(q_shape), (desc.b, desc.l, 2 * desc.w + 1),
+            band_workspace_bytes(desc, flags), load_library().banded_bmm)
+
+
 def banded_bmm(q, k, v, w, dilation=1, scale=1.0, mask_invalid=False, staged=False,
                out_dtype=torch.float32, return_s=False, out=None, ws=None, s_out=None,
                flags=0):
@@ -336,19 +376,20 @@ def banded_bmm(q, k, v, w, dilation=1, scale=1.0, mask_invalid=False, staged=Fal
             raise ValueError(f"{name} must be bfloat16")
         if t.shape != q.shape:
             raise ValueError("q, k, v must have the same shape")
-    desc = band_desc(tuple(q.shape), w, dilation, scale, out_dtype)
     flags |= (BAND_STAGED if staged or return_s else 0) | (BAND_MASK_INVALID if mask_invalid else 0)
+    desc, shape, s_shape, need, fn = _band_plan(q.shape, int(w), int(dilation), float(scale),
+                                                out_dtype, flags)
     if out is None:
-        out = torch.empty(tuple(q.shape), dtype=out_dtype, device=q.device)
+        out = torch.empty(shape, dtype=out_dtype, device=q.device)
     if return_s and s_out is None:
-        s_out = torch.empty((desc.b, desc.l, 2 * desc.w + 1), dtype=torch.float32, device=q.device)
-    need = band_workspace_bytes(desc, flags)
+        s_out = torch.empty(s_shape, dtype=torch.float32, device=q.device)
     if ws is None and need:
         ws = torch.empty(need, dtype=torch.uint8, device=q.device)
     ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
-    st = load_library().banded_bmm(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(out),
-                                   _ptr(s_out), _ptr(ws), ws_bytes, flags, _stream(q.device))
-    _check(st, "banded_bmm")
+    st = fn(desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), _ptr(s_out), _ptr(ws),
+            ws_bytes, flags, _stream(q.device))
+    if st != OK:
+        _check(st, "banded_bmm")
     return (out, s_out) if return_s else out
 
 

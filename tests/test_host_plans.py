@@ -1,0 +1,51 @@
+"""The binding's kept call plans: keyed by plain values, refusals stay refusals."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2208_02025_amd as ol
+
+X, W = torch.Size((2, 9, 8, 64)), torch.Size((3, 3, 24, 64))
+
+
+def _plan(**kw):
+    a = dict(stride=1, padding=1, dilation=1, output_padding=0, out_dtype=torch.float32, flags=0,
+             dtype=torch.bfloat16, x=X, w=W)
+    a.update(kw)
+    return ol._conv_plan("derived_conv2d", False, a["x"], a["w"], a["dtype"],
+                         ol._key(a["stride"]), ol._key(a["padding"]), ol._key(a["dilation"]),
+                         ol._key(a["output_padding"]), a["out_dtype"], a["flags"])
+
+
+@pytest.mark.parametrize("v", [[2, 1], (2, 1), np.array([2, 1]), torch.tensor([2, 1]),
+                               torch.Size((2, 1))])
+def test_key_holds_values(v):
+    k = ol._key(v)
+    assert k == (2, 1) and all(type(e) is int for e in k)
+
+
+def test_plan_matches_fresh_descriptor():
+    for kw in ({}, {"stride": 2}, {"padding": (0, 2)}, {"flags": ol.Y_BF16},
+               {"flags": ol.FUSE_EPILOGUE}, {"out_dtype": torch.bfloat16},
+               {"dtype": torch.float32}):
+        ref, shape, k, need, _, _ = _plan(**kw)
+        d = ol.conv_desc(X, W, kw.get("stride", 1), kw.get("padding", 1), 1, 0,
+                         kw.get("dtype", torch.bfloat16), kw.get("out_dtype", torch.float32))
+        assert bytes(ref._obj) == bytes(d) and ctypes.sizeof(d) == len(bytes(d))
+        assert shape == (2, *ol.conv_out_hw(d, False), 24) and k == 24
+        assert need == ol.conv_workspace_bytes(d, False, kw.get("flags", 0))
+
+
+def test_refusals_stay():
+    _plan()
+    for kw, err in (({"stride": 0}, ol.OllieError), ({"dilation": 0}, ol.OllieError),
+                    ({"w": torch.Size((3, 3, 24, 32))}, ValueError),
+                    ({"dtype": torch.float16}, ValueError),
+                    ({"out_dtype": torch.float64}, ValueError)):
+        for _ in range(2):      # a refusal is not kept either
+            with pytest.raises(err):
+                _plan(**kw)
+    with pytest.raises((TypeError, IndexError)):
+        ol._key(1.0)
