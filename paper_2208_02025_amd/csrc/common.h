@@ -128,6 +128,14 @@ __device__ __forceinline__ void buffer_copy16(const void* base, int nbytes, uint
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voff, soff, 0, 0);
 }
 
+// The same with 4 bytes per lane: lane L's float lands at dst + 4 L.
+__device__ __forceinline__ void buffer_copy4(const void* base, int nbytes, uint32_t voff,
+                                             int soff, lds_void* dst) {
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, nbytes, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 4, voff, soff, 0, 0);
+}
+
 // s_waitcnt with only the vector-memory counter constrained (expcnt, lgkmcnt at max).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

@@ -21,7 +21,7 @@
 //     an fp32 tile instead of 64-byte pieces of sixteen rows.  With k as short as it
 //     is here (256-512), Y's write is most of the kernel's HBM traffic.
 // bf16 fallback (any k % 8 == 0): register-staged double-buffered 128x128 tiles.
-// fp32 path: v_mfma_f32_16x16x4_f32 (small problems; any k).
+// fp32 path: the same pipeline on v_mfma_f32_16x16x4_f32 (any k).
 //
 // The MFMA is issued as D = Wt-tile x X-tile^T so that each lane ends up holding four
 // consecutive output columns n of one row m.
@@ -359,7 +359,110 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(
     store_tile<FM, FN, YT>(Y, acc, M, N, m0 + wm * WM, n0 + wn * WN);
 }
 
-// fp32 operands: 64x64 tile, 16-deep k-tile, scalar staged loads (any shape).
+// ------------------------------------------------------------------------ fp32 operands
+// The bf16 pipeline on fp32 rows: 32-deep k-tiles (the same 128-byte rows, chunk swizzle,
+// copy ring and row-wise epilogue) and v_mfma_f32_16x16x4_f32.  A 16-byte LDS read gives a
+// lane four consecutive k of its row, which feed four MFMAs: MFMA e contracts the k values
+// 4g + e over the lane groups g.  VEC = 4 copies 16-byte chunks (rows 16-byte aligned,
+// K % 4 == 0), VEC = 1 single floats at the same LDS places (any K).  Rows past M or N, and
+// k past K in the last k-tile, are given an offset past the buffer and read zeros.
+// Operands under 2 GiB each.
+// Scalar loads through registers with no overlap took 39.3 us at 25088 x 576 x 64 (a ResNet
+// stage-1 layer, batch 8) where this takes 22.4: 12 us of MFMA work at 153 TFLOP/s and the
+// 58 MB store of Y (9 us at the fill rate), which the two k-tiles of a tile overlap in part.
+// 12288 x 4608 x 128: 202 -> 132 us (110 TFLOP/s); 784 x 576 x 102, single floats: 11.0 -> 5.5.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int MINB, int VEC, typename YT>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, MINB)
+void gemm_nt_f32_dma_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                            YT* __restrict__ Y, int64_t M, int64_t N, int64_t K, int tiles_m,
+                            int tiles_n) {
+    constexpr int NW = WAVES_M * WAVES_N, NT = 64 * NW, BKF = 32;
+    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
+    constexpr int FM = WM / 16, FN = WN / 16;
+    constexpr int STAGE_CHUNKS = (BM + BN) * 8;           // A rows, then B rows
+    constexpr int LANES = 32 / VEC;                       // lanes per row of one copy
+    constexpr int RPI = 64 / LANES;                       // rows per wave-wide copy
+    constexpr int RSTEP = RPI * NW;                       // rows between a wave's copies
+    constexpr int A_LOADS = BM / RSTEP, B_LOADS = BN / RSTEP;
+    constexpr int LOADS = A_LOADS + B_LOADS;
+    static_assert(BM % RSTEP == 0 && BN % RSTEP == 0 && RSTEP % 8 == 0, "whole wave copies");
+    static_assert((NSTAGE - 1) * LOADS < 64, "vmcnt range");
+    __shared__ u32x4 lds[NSTAGE * STAGE_CHUNKS];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    int tm, tn;
+    tile_of(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+
+    // this lane's place in a copy: row lrow (the same modulo 8 in every copy), k offset lk
+    const int lrow = wave * RPI + lane / LANES;
+    const int lpos = (lane % LANES) * VEC;
+    const int lk = (((lpos >> 2) ^ (lrow & 7)) << 2) + (lpos & 3);
+    const uint32_t row_bytes = (uint32_t)K * 4;
+    const uint32_t aoff = (uint32_t)((m0 + lrow) * K + lk) * 4;
+    const uint32_t boff = (uint32_t)((n0 + lrow) * K + lk) * 4;
+    const int a_bytes = (int)(M * K * 4), b_bytes = (int)(N * K * 4);
+    auto issue = [&](int kt, int buf) {
+        // offsets stay below 2^31 + a tile's rows; bit 31 puts them past either buffer
+        const uint32_t tail = kt * BKF + lk >= (int)K ? 0x80000000u : 0u;
+        u32x4* dst = lds + buf * STAGE_CHUNKS;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const bool is_a = i < A_LOADS;
+            const int r = is_a ? i : i - A_LOADS;
+            const uint32_t off = ((is_a ? aoff : boff) + r * RSTEP * row_bytes + kt * BKF * 4) | tail;
+            lds_void* to = (lds_void*)(dst + ((is_a ? 0 : BM) + r * RSTEP + wave * RPI) * 8);
+            if constexpr (VEC == 4)
+                buffer_copy16(is_a ? A : B, is_a ? a_bytes : b_bytes, off, 0, to);
+            else
+                buffer_copy4(is_a ? A : B, is_a ? a_bytes : b_bytes, off, 0, to);
+        }
+    };
+
+    f32x4 acc[FN][FM];
+#pragma unroll
+    for (int i = 0; i < FN; ++i)
+#pragma unroll
+        for (int j = 0; j < FM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    const int ktiles = (int)((K + BKF - 1) / BKF);
+#pragma unroll
+    for (int s = 0; s < NSTAGE - 1; ++s)
+        if (s < ktiles) issue(s, s);
+    for (int kt = 0; kt < ktiles; ++kt) {
+        if (kt + NSTAGE - 2 < ktiles) wait_vmcnt<(NSTAGE - 2) * LOADS>();
+        else wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+        if (kt + NSTAGE - 1 < ktiles) issue(kt + NSTAGE - 1, (kt + NSTAGE - 1) % NSTAGE);
+        const f32x4* la = reinterpret_cast<const f32x4*>(lds + (kt % NSTAGE) * STAGE_CHUNKS);
+        const f32x4* lb = la + BM * 8;
+#pragma unroll
+        for (int kk = 0; kk < BKF / 16; ++kk) {
+            const int ch = kk * 4 + (lane >> 4);
+            f32x4 fa[FN], fb[FM];
+#pragma unroll
+            for (int i = 0; i < FN; ++i) fa[i] = lb[swz(wn * WN + i * 16 + (lane & 15), ch)];
+#pragma unroll
+            for (int j = 0; j < FM; ++j) fb[j] = la[swz(wm * WM + j * 16 + (lane & 15), ch)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < FN; ++i)
+#pragma unroll
+                    for (int j = 0; j < FM; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][e], fb[j][e],
+                                                                         acc[i][j], 0, 0, 0);
+        }
+    }
+    store_tile_rows<BM, BN, NT, NSTAGE * STAGE_CHUNKS, WM, WN, FM, FN, YT>(Y, acc, lds, M, N, m0,
+                                                                           n0, wm, wn);
+}
+
+// fp32 operands of 2 GiB or more: 64x64 tile, 16-deep k-tile, scalar staged loads with
+// 64-bit addresses (any shape).
 template <typename YT>
 __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ B, YT* __restrict__ Y,
@@ -458,9 +561,27 @@ hipError_t go_bf16(int64_t m, int64_t n, int64_t k, const void* a, const void* b
     return hipGetLastError();
 }
 
+template <int BM, int BN, int WAVES_M, int WAVES_N, int MINB, int VEC, typename YT>
+hipError_t go_f32_dma(int64_t m, int64_t n, int64_t k, const void* a, const void* b, void* y,
+                      hipStream_t stream) {
+    int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
+    hipLaunchKernelGGL((gemm_nt_f32_dma_kernel<BM, BN, WAVES_M, WAVES_N, 2, MINB, VEC, YT>),
+                       dim3(tiles_m * tiles_n), dim3(64 * WAVES_M * WAVES_N), 0, stream,
+                       (const float*)a, (const float*)b, (YT*)y, m, n, k, tiles_m, tiles_n);
+    return hipGetLastError();
+}
+
 template <typename YT>
 hipError_t go_f32(int64_t m, int64_t n, int64_t k, const void* a, const void* b, void* y,
                   hipStream_t stream) {
+    if (m * k * 4 < (int64_t(1) << 31) && n * k * 4 < (int64_t(1) << 31)) {
+        // One tile shape for every size, 64x64 in four 16x64 waves, five workgroups per CU
+        // (32 KB of LDS each) whose copies, products and stores overlap: 25088x576x64 22.4 us
+        // (4 x 32x32 waves 24.5, 128x64 tiles 22.9-27.6, 128x128 26.0-28.0, three copy stages
+        // 24.1), 12288x4608x128 132 us (129-141), 196x144x16 3.2 us (3.2-6.8).
+        return k % 4 == 0 ? go_f32_dma<64, 64, 4, 1, 5, 4, YT>(m, n, k, a, b, y, stream)
+                          : go_f32_dma<64, 64, 4, 1, 5, 1, YT>(m, n, k, a, b, y, stream);
+    }
     int tiles_m = (int)((m + 63) / 64), tiles_n = (int)((n + 63) / 64);
     hipLaunchKernelGGL((gemm_nt_f32_kernel<YT>), dim3(tiles_m * tiles_n), dim3(256), 0, stream,
                        (const float*)a, (const float*)b, (YT*)y, m, n, k, tiles_m, tiles_n);

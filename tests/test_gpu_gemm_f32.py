@@ -1,0 +1,33 @@
+"""The fp32 GEMM stage at the ends of its tiles and k-tiles, against fp64 torch on the same
+inputs.  Tolerance: k fp32 products summed in any order err by at most about k * 2^-24 of
+the sum of their magnitudes; integer inputs are exact."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 1, 1), (1, 64, 4), (63, 65, 3), (64, 64, 32), (65, 63, 33), (128, 17, 31),
+          (196, 144, 16), (100, 70, 36), (257, 129, 102), (5, 300, 64), (700, 513, 68),
+          (33, 40, 127)]
+
+
+@pytest.mark.parametrize("m,n,k", SHAPES)
+@pytest.mark.parametrize("y_dtype", [torch.float32, torch.bfloat16])
+def test_gemm_f32_edges(m, n, k, y_dtype):
+    import paper_2208_02025_amd as ol
+    g = torch.Generator().manual_seed(m * 1000 + n + k)
+    # operands end where their buffers end: a read past a row's end would show as NaN
+    def buf(r, c, t):
+        big = torch.full((r * c + 256,), float("nan"))
+        big[:r * c] = t.reshape(-1)
+        return big.cuda()[:r * c].view(r, c)
+    ai = torch.randint(-3, 4, (m, k), generator=g).float()
+    bi = torch.randint(-3, 4, (n, k), generator=g).float()
+    y = torch.full((m, n), float("nan"), dtype=y_dtype, device="cuda")
+    ol.gemm_nt(buf(m, k, ai), buf(n, k, bi), out=y)
+    ref = (ai.double() @ bi.double().t()).to(y_dtype)
+    assert torch.equal(y.cpu(), ref)
+    a, b = torch.randn(m, k, generator=g), torch.randn(n, k, generator=g)
+    out = ol.gemm_nt(buf(m, k, a), buf(n, k, b)).cpu().double()
+    bound = k * 2.0 ** -24 * (a.double().abs() @ b.double().abs().t())
+    assert ((out - a.double() @ b.double().t()).abs() <= bound + 1e-30).all()
