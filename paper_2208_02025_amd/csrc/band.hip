@@ -1145,14 +1145,27 @@ hipError_t launch_fused_half(const BandGeom& g, const void* q, const void* k, co
     return hipGetLastError();
 }
 
-// Wave shapes: 0 = four waves of 32 queries (the default: measured faster than eight
-// waves, which have half the copies per query but the same occupancy and twice the LDS
-// per workgroup), 1 = four waves of 64 queries, 2 = two waves of 64 queries (half the
-// LDS reads per score, two waves per SIMD), 3 = four waves of 32 queries over 32-key
-// halves (band_fused_half_kernel).  `shape` (0..3, from the caller's flags; -1 =
-// automatic) overrides the choice for tuning sweeps and tests.
+// Wave shapes: 0 = four waves of 32 queries (the default on large grids: measured faster
+// than eight waves, which have half the copies per query but the same occupancy and twice
+// the LDS per workgroup), 1 = four waves of 64 queries, 2 = two waves of 64 queries (half
+// the LDS reads per score, two waves per SIMD), 3 = four waves of 32 queries over 32-key
+// halves (band_fused_half_kernel).  `shape` (0..3, from the caller's flags; -1 = automatic)
+// overrides the choice for tuning sweeps and tests.
+//
+// Automatic choice: four waves of 16 queries (64-query tiles) below 704 tiles of 128
+// queries, 2.75 per CU.  There too few waves are resident to hide a block's serial chain
+// (scores, maximum, exponentials, products), and halving a wave's queries halves the chain
+// and doubles the waves; above, sharing each key fragment between two query groups wins.
+// Shape 0 / 16-query waves, us: 8 tiles of l 512 w 256 14.0 / 9.0, b 12 l 3001 w 200 dil 3
+// masked (288 tiles) 19.4 / 15.4, b 40 l 2000 w 100 dil 2 (640 tiles) 20.5 / 18.8,
+// b 24 l 4096 w 256 (768 tiles) 26.2 / 27.1, 96 x 4096 w 256 dil 2 (3072 tiles) 94 / 104.
+// Two key shares per query group, merged at the end, gained only on a few tiles (9.0 / 7.9)
+// and lost from 200 on; deeper copy rings lost everywhere.
 hipError_t launch_band_fused(const BandGeom& g, const void* q, const void* k, const void* v,
                              void* o, int o_bf16, int mask, int shape, hipStream_t stream) {
+    const int64_t l0 = (g.l + g.dil - 1) / g.dil;
+    if (shape < 0 && (l0 + 127) / 128 * g.dil * g.b < 704)
+        return launch_fused_nw<4, 1>(g, q, k, v, o, o_bf16, mask, stream);
     const int cfg = shape < 0 ? 0 : shape;
     if (cfg == 3) return launch_fused_half(g, q, k, v, o, o_bf16, mask, stream);
     if (cfg == 1) return launch_fused_nw<4, 4>(g, q, k, v, o, o_bf16, mask, stream);
