@@ -437,12 +437,22 @@ __global__ __launch_bounds__(64 * NW) void band_gbmm_kernel(BandGeom g, int ntx,
 // Softmax bookkeeping per query, in log2 units (x = scale*log2(e)*score): a running
 // reference m, and the denominator and O both accumulated unnormalised by MFMA -- the
 // denominator as the product of an all-ones operand with the same bf16 probabilities
-// that multiply V, so O and its normaliser see identical rounding.  m is raised only
-// when a score exceeds it by more than kLazy; the test uses each lane's own maximum,
-// and only when it fires is the row maximum formed across the row's 4 lanes.  The
-// scale enters as one FMA per score; a negative scale is handled by negating the query
+// that multiply V, so O and its normaliser see identical rounding.  A wave takes its
+// references from its first blocks (row maxima over the row's 4 lanes) and compares no
+// later score with them: any reference within 2^127 of the row's largest score gives the
+// same relative precision, so the comparisons (24 of ~112 VALU instructions a block, and a
+// reduction between the scores and the exponentials) only guard against overflow.  Where one
+// happened (the denominator or O is not finite at the end) the tile is evaluated again with
+// every score compared: m is then raised whenever a score exceeds it by more than kLazy;
+// the test uses each lane's own maximum, and only when it fires is the row maximum formed.
+// The scale enters as one FMA per score; a negative scale is handled by negating the query
 // fragments (an exact sign flip of bf16) and using |scale|.  Band and range masks are
 // applied in place, only on blocks that cross an edge.
+//
+// What bounds it (96 x 4096, w 256, dilation 2; 94.3 us before, 88.5 now): 85 k VALU and
+// 62 k MFMA cycles per SIMD of ~170 k, which overlap in part, against ~336 MB of HBM traffic
+// (66 us at the copy rate): left out one at a time, the copies are worth 12 us, the stores
+// of O 14, the P*V products 10.
 //
 // LDS slot layout: 512 16-byte chunks of K, then 512 of V; chunk c of key row r sits
 // at r*8 + (c ^ (r & 7)) (an XOR swizzle: the 16-lane fragment reads of K and the
@@ -474,6 +484,19 @@ __device__ __forceinline__ void block_sync() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+}
+
+// f(Const<0>{}), ..., f(Const<N - 1>{})
+template <int I>
+struct Const {
+    static constexpr int value = I;
+};
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(Const<I>{});
+        static_for<N, I + 1>(f);
+    }
 }
 
 template <typename OT, bool MASK, int kSlots, int NW, bool BUF, int HQ>
@@ -547,8 +570,8 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
     // launch takes this form only when every such offset fits in 32 bits.
     const int nrec = BUF ? (t.lr - 1) * (int)row_bytes + kD * 2 : 0;
     const int voff0 = BUF ? tt0 * (int)row_bytes + dch * 16 : 0;
-    auto dma = [&](int kb) {
-        u32x4* slot = lds + (kb % kSlots) * kSlotChunks;
+    auto dma_block = [&](int it, int kb) {
+        u32x4* slot = lds + (it % kSlots) * kSlotChunks;
         if constexpr (BUF) {
 #pragma unroll
             for (int e = 0; e < kPass; ++e) {
@@ -587,6 +610,11 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
             }
         }
     };
+    // Iteration it handles key block (it - q0 / 64) mod nblk, so that the tiles that share a
+    // block read it in the same iteration, while it is in L2 (90.5 -> 88.5 us)
+    const int first = (t.q0 / kT) % nblk;
+    auto block_of = [&](int it) { const int x = it - first; return x < 0 ? x + nblk : x; };
+    auto dma = [&](int it) { dma_block(it, block_of(it)); };
     // LDS byte offsets (within a slot) of this lane's fragment reads
     //   K fragment (ft, kk): key row 16ft + li, chunk 4kk + grp
     //   V^T fragment (h, eb, i): key row 32h + 16i + 4grp + li/4, 8 bytes at column
@@ -603,6 +631,8 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
     }
     const char* lds_b = reinterpret_cast<const char*>(lds);
     const uint32_t lds_a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)lds;
+#pragma unroll
+    for (int eb = 0; eb < 4; ++eb) voff[eb] += (int)lds_a;   // LDS byte addresses in slot 0
     // waits until at most `later` blocks (2*kPass copies each per lane) are in flight
     auto wait_blocks = [](int later) {
         static_assert(kSlots >= 2 && kSlots <= 6, "slot count");
@@ -625,8 +655,8 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
     const bf16x8 ones = __builtin_bit_cast(bf16x8, (u32x4){0x3f803f80u, 0x3f803f80u,
                                                           0x3f803f80u, 0x3f803f80u});
 
-    auto read_k = [&](int kb, bf16x8 (&kf)[4][2]) {
-        const char* sb = lds_b + (kb % kSlots) * kSlotChunks * 16;
+    auto read_k = [&](auto slot, bf16x8 (&kf)[4][2]) {
+        const char* sb = lds_b + decltype(slot)::value * kSlotChunks * 16;
 #pragma unroll
         for (int ft = 0; ft < 4; ++ft)
 #pragma unroll
@@ -645,62 +675,85 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
             }
     };
 
-    // One block iteration: scores, softmax and P*V of block kb.
-    auto step = [&](int kb) {
+    // Whether a query of the wave has no reference yet (its reference is -inf)
+    bool unset = true;
+    auto no_reference = [&]() {
+        bool n = false;
+#pragma unroll
+        for (int hq = 0; hq < HQ; ++hq)
+            n = n || (m_run[hq] == -INFINITY && qa + hq * 16 + li < t.lr);
+        return __any(n) != 0;
+    };
+
+    // One block iteration: scores, softmax and P*V of block kb, which lies in slot `slot`.
+    auto step = [&](int kb, auto slot, bool checked) {
+        constexpr int kSlot = decltype(slot)::value;
         const int t0 = t.q0 - w + kb * kT;
         f32x4 s[HQ][4];
         {
             bf16x8 kf[4][2];
-            read_k(kb, kf);
+            read_k(slot, kf);
             scores(kf, s);
         }
-        bool full = t0 >= qa + kQW - 1 - w && t0 + kT - 1 <= qa + w;
-        if (MASK) full = full && t0 >= 0 && t0 + kT <= t.lr;
-        if (!full) {                               // band (and range) mask, in place
+        // band (and range) mask, in place, on blocks that cross an edge: key c = 16ft + v of
+        // the lane's 4grp-based run is inside from lower to upper (two instructions a score)
+        const bool below = t0 < qa + kQW - 1 - w || (MASK && t0 < 0);
+        const bool above = t0 + kT - 1 > qa + w || (MASK && t0 + kT > t.lr);
+        if (below) {
 #pragma unroll
             for (int hq = 0; hq < HQ; ++hq) {
-                const int base = t0 + 4 * grp - (qa + hq * 16 + li) + w;
+                int lower = (qa + hq * 16 + li) - w - t0 - 4 * grp;
+                if (MASK) lower = max(lower, -t0 - 4 * grp);
 #pragma unroll
                 for (int ft = 0; ft < 4; ++ft)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        bool ok = (unsigned)(base + ft * 16 + v) <= (unsigned)(2 * w);
-                        if (MASK) {
-                            const int tt = t0 + ft * 16 + 4 * grp + v;
-                            ok = ok && tt >= 0 && tt < t.lr;
-                        }
-                        s[hq][ft][v] = ok ? s[hq][ft][v] : -INFINITY;
-                    }
+                    for (int v = 0; v < 4; ++v)
+                        s[hq][ft][v] = ft * 16 + v >= lower ? s[hq][ft][v] : -INFINITY;
             }
         }
-        float mb[HQ];
-#pragma unroll
-        for (int hq = 0; hq < HQ; ++hq) {
-            mb[hq] = -INFINITY;
-#pragma unroll
-            for (int ft = 0; ft < 4; ++ft)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) mb[hq] = fmaxf(mb[hq], s[hq][ft][v]);
-        }
-        // lazy reference update; the row maximum (4 lanes) only when a lane asks for it
-        bool up = false;
-#pragma unroll
-        for (int hq = 0; hq < HQ; ++hq) up = up || mb[hq] * sl2 > m_run[hq] + kLazy;
-        if (__any(up)) {
+        if (above) {
 #pragma unroll
             for (int hq = 0; hq < HQ; ++hq) {
-                float m = mb[hq];
-                m = fmaxf(m, __int_as_float(__builtin_amdgcn_ds_bpermute(xor16, __float_as_int(m))));
-                m = fmaxf(m, __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(m))));
-                const float mbx = m * sl2;
-                const float m_new = mbx > m_run[hq] + kLazy ? mbx : m_run[hq];
-                const float corr =
-                    m_new == m_run[hq] ? 1.f : __builtin_amdgcn_exp2f(m_run[hq] - m_new);
-                lsum[hq] *= corr;
+                int upper = (qa + hq * 16 + li) + w - t0 - 4 * grp;
+                if (MASK) upper = min(upper, t.lr - 1 - t0 - 4 * grp);
 #pragma unroll
-                for (int eb = 0; eb < 4; ++eb) o[hq][eb] *= corr;
-                m_run[hq] = m_new;
+                for (int ft = 0; ft < 4; ++ft)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        s[hq][ft][v] = ft * 16 + v <= upper ? s[hq][ft][v] : -INFINITY;
             }
+        }
+        if (checked || unset) {
+            float mb[HQ];   // each lane's maximum of the block
+#pragma unroll
+            for (int hq = 0; hq < HQ; ++hq) {
+                mb[hq] = -INFINITY;
+#pragma unroll
+                for (int ft = 0; ft < 4; ++ft)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) mb[hq] = fmaxf(mb[hq], s[hq][ft][v]);
+            }
+            // lazy reference update; the row maximum (4 lanes) only when a lane asks for it
+            bool up = false;
+#pragma unroll
+            for (int hq = 0; hq < HQ; ++hq) up = up || mb[hq] * sl2 > m_run[hq] + kLazy;
+            if (__any(up)) {
+#pragma unroll
+                for (int hq = 0; hq < HQ; ++hq) {
+                    float m = mb[hq];
+                    m = fmaxf(m, __int_as_float(__builtin_amdgcn_ds_bpermute(xor16, __float_as_int(m))));
+                    m = fmaxf(m, __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(m))));
+                    const float mbx = m * sl2;
+                    const float m_new = mbx > m_run[hq] + kLazy ? mbx : m_run[hq];
+                    const float corr =
+                        m_new == m_run[hq] ? 1.f : __builtin_amdgcn_exp2f(m_run[hq] - m_new);
+                    lsum[hq] *= corr;
+#pragma unroll
+                    for (int eb = 0; eb < 4; ++eb) o[hq][eb] *= corr;
+                    m_run[hq] = m_new;
+                }
+            }
+            if (unset) unset = no_reference();
         }
         bf16x8 pf[HQ][2];
 #pragma unroll
@@ -719,14 +772,12 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
             }
         }
         // P*V per 32-key half h: V^T fragments from key rows 32h and 32h + 16 of the slot
-        const uint32_t vb = lds_a + (kb % kSlots) * kSlotChunks * 16;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        static_for<2>([&](auto hc) {
+            constexpr int h = decltype(hc)::value, kOff = kSlot * kSlotChunks * 16 + h * 32 * 128;
             bf16x8 vf[4];
 #pragma unroll
             for (int eb = 0; eb < 4; ++eb) {
-                const uint32_t a = vb + voff[eb] + h * 32 * 128;
-                s16x4 r[2] = {tr_read_raw<0>(a), tr_read_raw<16 * 128>(a)};
+                s16x4 r[2] = {tr_read_raw<kOff>(voff[eb]), tr_read_raw<kOff + 16 * 128>(voff[eb])};
                 vf[eb] = __builtin_bit_cast(bf16x8, r);
             }
             lds_wait(vf);
@@ -740,30 +791,94 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
             for (int hq = 0; hq < HQ; ++hq)
                 lsum[hq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[hq][h], lsum[hq],
                                                                    0, 0, 0);
-        }
+        });
     };
-    // prologue: blocks 0 .. kSlots-2 in flight, block 0 resident before the loop
-#pragma unroll
-    for (int b = 0; b < kSlots - 1; ++b)
-        if (b < nblk) dma(b);
-    wait_blocks(min(nblk - 1, kSlots - 2));
-    block_sync();
-    for (int kb = 0; kb < nblk; ++kb) {
-        if (kb + kSlots - 1 < nblk) dma(kb + kSlots - 1);
-        if (kb >= lo && kb <= hi) step(kb);          // the block meets the wave's band
-        // block kb + 1 is read by the next iteration: its copies must have landed; those
-        // of the blocks after it may still be in flight
-        wait_blocks(min(nblk - 1, kb + kSlots - 1) - (kb + 1));
+    auto iterate = [&](int it, auto slot, bool checked) {
+        if (it + kSlots - 1 < nblk) dma(it + kSlots - 1);
+        const int kb = block_of(it);
+        if (kb >= lo && kb <= hi) step(kb, slot, checked);   // the block meets the wave's band
+        // iteration it + 1 reads next: its copies must have landed; those of the iterations
+        // after it may still be in flight
+        wait_blocks(min(nblk - 1, it + kSlots - 1) - (it + 1));
         block_sync();
+    };
+    // One pass over the key blocks.  Unless `checked`, a wave takes its references from its
+    // first blocks and compares no further score with them.
+    auto pass = [&](bool checked) {
+#pragma unroll
+        for (int hq = 0; hq < HQ; ++hq) {
+            lsum[hq] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            m_run[hq] = -INFINITY;
+#pragma unroll
+            for (int eb = 0; eb < 4; ++eb) o[hq][eb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+        unset = true;
+        // prologue: blocks 0 .. kSlots-2 in flight, block 0 resident before the loop
+#pragma unroll
+        for (int b = 0; b < kSlots - 1; ++b)
+            if (b < nblk) dma(b);
+        wait_blocks(min(nblk - 1, kSlots - 2));
+        block_sync();
+        for (int it = 0; it < nblk; it += kSlots)
+            static_for<kSlots>([&](auto slot) {
+                if (it + decltype(slot)::value < nblk)
+                    iterate(it + decltype(slot)::value, slot, checked);
+            });
+    };
+    pass(false);
+    // A score more than ~127 log2 units above its row's reference made p, and with it the
+    // denominator or O, infinite (so does an infinite or NaN input).  The tile is then
+    // evaluated again with every score compared; the waves of the workgroup agree on it
+    // through the idle ring.
+    {
+        float bad = 0.f;
+#pragma unroll
+        for (int hq = 0; hq < HQ; ++hq) {
+            if (qa + hq * 16 + li >= t.lr) continue;
+            bad += lsum[hq][0] * 0.f;
+#pragma unroll
+            for (int eb = 0; eb < 4; ++eb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) bad += o[hq][eb][v] * 0.f;
+        }
+        const bool redo = __any(bad != 0.f) != 0;          // NaN: not finite
+        uint32_t* flag = reinterpret_cast<uint32_t*>(lds + kSlots * kSlotChunks) - NW;
+        if (lane == 0) flag[wv] = redo;
+        __syncthreads();
+        uint32_t any = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) any |= flag[i];
+        if (__builtin_amdgcn_readfirstlane(any)) {
+            __syncthreads();                               // the flags are read
+            pass(true);
+        }
     }
+    // O leaves through the idle ring, 16 queries at a time, so that a store instruction
+    // writes whole rows (256 bytes in fp32) instead of a quarter of 16 rows each
+    constexpr int kRowCh = kD * (int)sizeof(OT) / 16, kRowsPer = 64 / kRowCh;
+    static_assert(NW * 16 * kRowCh * 16 + NW * 4 <= kSlots * kSlotChunks * 16, "O patch");
+    char* patch = reinterpret_cast<char*>(lds) + wv * 16 * kRowCh * 16;
 #pragma unroll
     for (int hq = 0; hq < HQ; ++hq) {
-        const int q = qa + hq * 16 + li;
-        if (q >= t.lr) continue;
         const float inv = 1.f / lsum[hq][0];
-        OT* orow = O + row_off(g, t, q);
 #pragma unroll
-        for (int eb = 0; eb < 4; ++eb) Out<OT>::put4(orow + eb * 16 + 4 * grp, o[hq][eb] * inv);
+        for (int eb = 0; eb < 4; ++eb) {
+            const int byte = (eb * 16 + 4 * grp) * (int)sizeof(OT);
+            Out<OT>::put4(reinterpret_cast<OT*>(patch + li * kRowCh * 16 +
+                                                ((byte >> 4) ^ (li & (kRowCh - 1))) * 16 + (byte & 15)),
+                          o[hq][eb] * inv);
+        }
+        wave_lds_order();
+#pragma unroll
+        for (int n = 0; n < 16 / kRowsPer; ++n) {
+            const int row = n * kRowsPer + lane / kRowCh, ch = lane % kRowCh;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(patch + row * kRowCh * 16 +
+                                                            (ch ^ (row & (kRowCh - 1))) * 16);
+            const int q = qa + hq * 16 + row;
+            if (q < t.lr)
+                *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(O + row_off(g, t, q)) + ch * 16) = v;
+        }
+        wave_lds_order();
     }
 }
 

@@ -1,6 +1,10 @@
-"""The 16-query waves that the fused band takes on small grids against the 32-query waves
-(BAND_SHAPE(0)): the same key blocks in the same order, so the same bits; and the largest
-grid on each side of the choice."""
+"""The fused band: the 16-query waves of small grids against the 32-query waves
+(BAND_SHAPE(0)), with the largest grid on each side of the choice; scores that overflow the
+references taken from a row's first blocks; non-finite inputs.
+
+Tolerance: both forms round each probability to bf16 against a reference of their own, so
+each is within 2^-9 of every probability, relatively, and O within 2^-8 of max |V| of the
+other's (2^-7 with the rounding of a bf16 O on top)."""
 import pytest
 import torch
 
@@ -22,4 +26,49 @@ def test_small_grid_waves(b, l, w, dil, mask):
         ol.banded_bmm(q, k, v, w, dil, 0.125, mask_invalid=mask, out_dtype=out_dtype, out=got)
         ref = ol.banded_bmm(q, k, v, w, dil, 0.125, mask_invalid=mask, out_dtype=out_dtype,
                             flags=ol.BAND_SHAPE(0))
-        assert torch.equal(got, ref)
+        assert (got.float() - ref.float()).abs().max() <= 2.0 ** -7 * v.float().abs().max()
+
+
+def _dense(q, k, v, w, scale):
+    """fp64 zero-mode band attention (dilation 1) from its definition."""
+    q, k, v = (t.double() for t in (q, k, v))
+    b, l, _ = q.shape
+    pad = torch.zeros(b, w, 64, dtype=torch.float64, device=q.device)
+    kp, vp = torch.cat([pad, k, pad], 1), torch.cat([pad, v, pad], 1)
+    s = torch.bmm(q, kp.transpose(1, 2).contiguous()) * scale
+    i = torch.arange(l, device=q.device)[:, None]
+    j = torch.arange(l + 2 * w, device=q.device)[None, :]
+    s = s.masked_fill((j < i) | (j > i + 2 * w), -float("inf"))
+    return torch.bmm(torch.softmax(s, 2), vp)
+
+
+@pytest.mark.parametrize("b", [2, 300])
+@pytest.mark.parametrize("scale", [1.0, -1.0, 8.0])
+def test_scores_beyond_first_references(b, scale):
+    """Keys that grow along the sequence (and shrink, for the negative scale): later blocks
+    exceed the first ones' scores by thousands of log2 units."""
+    import paper_2208_02025_amd as ol
+    g = torch.Generator().manual_seed(b)
+    l, w = 300, 100
+    q, k, v = (torch.randn(b, l, 64, generator=g) for _ in range(3))
+    k = k * torch.linspace(0.1, 60.0, l)[None, :, None]
+    k[::2] = k[::2].flip(1)
+    q, k, v = (t.bfloat16().cuda() for t in (q, k, v))
+    out = ol.banded_bmm(q, k, v, w, 1, scale)
+    ref = _dense(q, k, v, w, scale)
+    # fp32 scores of up to ~2^15 carry 2^-9 absolute, p then 2^-8 relative besides its bf16
+    # rounding: within 2^-6 of max |V|
+    assert (out.double() - ref).abs().max() <= 2.0 ** -6 * v.double().abs().max() * abs(scale)
+
+
+@pytest.mark.parametrize("b", [1, 400])
+def test_nonfinite_query_stays_local(b):
+    import paper_2208_02025_amd as ol
+    g = torch.Generator().manual_seed(9)
+    q, k, v = (torch.randn(b, 256, 64, generator=g).bfloat16().cuda() for _ in range(3))
+    q[0, 100, 3] = float("nan")
+    out = ol.banded_bmm(q, k, v, 20, 1, 0.125)
+    bad = ~torch.isfinite(out)
+    ref = torch.zeros_like(bad)
+    ref[0, 100] = True
+    assert torch.equal(bad, ref)
