@@ -291,13 +291,13 @@ void conv_cols_kernel(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W
     }
 
     wait_vm<0>();    // no copy into LDS may still be in flight from here on
-    // each k-group owns every KW-th fragment: it hands the others over through LDS
+    // each k-group owns every KW-th row: it hands the others over through LDS
     f32x4* red = reinterpret_cast<f32x4*>(lds) + wo * F * (KW - 1) * 64 + lane;
     if constexpr (KW > 1) {
         block_barrier();
 #pragma unroll
         for (int f = 0; f < F; ++f) {
-            const int own = f % KW;
+            const int own = (f / NF) % KW;
             if (kg != own) red[(f * (KW - 1) + (kg < own ? kg : kg - 1)) * 64] = acc[f / NF][f % NF];
         }
         block_barrier();
@@ -312,8 +312,9 @@ void conv_cols_kernel(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W
     for (int own = 0; own < KW; ++own) {
         if (kg != own) continue;
 #pragma unroll
-        for (int i = own; i < F; i += KW) {
+        for (int i = 0; i < F; ++i) {
             const int y = i / NF, f = i % NF;
+            if (y % KW != own) continue;
             f32x4 v = acc[y][f];
 #pragma unroll
             for (int g = 0; g < KW - 1; ++g) v += red[(i * (KW - 1) + g) * 64];
