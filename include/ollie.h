@@ -303,7 +303,9 @@ int ollie_derived_conv_transpose2d_ex(const ollie_conv_desc* desc, const void* x
  * Default: one fused kernel, S and P never leave the chip, ws may be NULL and
  * s_out must be NULL.  With OLLIE_BAND_STAGED: three kernels (G2BMM -> softmax
  * eOperator -> band-times-dense) through fp32 S and bf16 P in ws; if s_out is not
- * NULL, S [b][l][2w+1] fp32 is written there instead of into ws. */
+ * NULL, S [b][l][2w+1] fp32 is written there instead, by one kernel that also evaluates
+ * the softmax and O from the scores it holds (the three stages fused around their S; ws is
+ * required as before and left as it is). */
 int banded_bmm(const ollie_band_desc* desc, const void* q, const void* k, const void* v,
                void* o, float* s_out, void* ws, size_t ws_bytes, uint32_t flags,
                void* stream);

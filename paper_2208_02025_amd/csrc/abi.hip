@@ -612,7 +612,12 @@ int banded_bmm(const ollie_band_desc* desc, const void* q, const void* k, const 
                     ws_bytes);
     if (!aligned16(ws) || (s_out && !aligned16(s_out)))
         return fail(OLLIE_EALIGN, "workspace and s_out must be 16-byte aligned");
-    float* sbuf = s_out ? s_out : (float*)ws;
+    if (s_out) {
+        hipError_t e = launch_band_scores(g, q, k, v, o, s_out, o_bf16, mask, s);
+        if (e != hipSuccess) return hip_fail(e, "band scores launch");
+        return OLLIE_OK;
+    }
+    float* sbuf = (float*)ws;
     void* pbuf = (char*)ws + band_p_offset(desc);
     hipError_t e = launch_band_g2bmm(g, q, k, sbuf, s);
     if (e != hipSuccess) return hip_fail(e, "G2BMM launch");

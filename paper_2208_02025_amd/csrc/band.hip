@@ -172,46 +172,26 @@ __device__ __forceinline__ void wave_lds_order() {
 // [0, 2w] are stored entry by entry, the rest as one 16-byte store each: every
 // instruction writes four 256-byte runs.
 constexpr int kSLd = kT + 4;   // patch row: 4 carried scores, then the block's 64
-template <int NW>   // waves per workgroup: a tile of 16*NW queries
-__global__ __launch_bounds__(64 * NW) void band_g2bmm_kernel(BandGeom g, int ntx,
-                                                            const bf16_t* __restrict__ Q,
-                                                            const bf16_t* __restrict__ K,
-                                                            float* __restrict__ S) {
-    constexpr int NT = 64 * NW, FT = 16 * NW;
-    __shared__ u32x4 lk[kT * 8];
-    __shared__ __attribute__((aligned(16))) float ls[NW][16 * kSLd];
-    Tile t;
-    if (!tile_of<FT>(g, ntx, t)) return;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, grp = lane >> 4;
-    const int qw = t.q0 + wv * 16;                  // the wave's first query
-    const int w = (int)g.w, nb = 2 * w + 1;
-    bf16x8 qf[2];
-    load_q_frags(g, t, Q, qw + (lane & 15), qf);
-    const int nblk = n_key_blocks<FT>(g);
-    float* patch = ls[wv];
-    // chunk-store slots: instruction n, lane -> row rr = 4n + lane/16, chunk c = lane%16
-    const int cc = lane & 15;
-    int64_t rbase[4];                               // S offset of row rr (-1: no row)
+struct SRows {
+    int64_t rbase[4];   // S offset of the chunk-store rows rr = 4n + lane/16 (-1: no row)
+
+    __device__ __forceinline__ void init(const BandGeom& g, const Tile& t, int qw) {
+        const int lane = threadIdx.x & 63, nb = 2 * (int)g.w + 1;
 #pragma unroll
-    for (int n = 0; n < 4; ++n) {
-        const int qq = qw + 4 * n + (lane >> 4);
-        rbase[n] = qq < t.lr ? row_index(g, t, qq) * nb : -1;
+        for (int n = 0; n < 4; ++n) {
+            const int qq = qw + 4 * n + (lane >> 4);
+            rbase[n] = qq < t.lr ? row_index(g, t, qq) * nb : -1;
+        }
     }
-    KVRegs r;
-    gload_block<true, false, NT>(g, t, K, nullptr, t.q0 - w, r);
-    for (int kb = 0; kb < nblk; ++kb) {
-        const int t0 = t.q0 - w + kb * kT;
-        __syncthreads();
-        lstore_block<true, false, NT>(r, lk, nullptr);
-        __syncthreads();
-        // the next key block's loads overlap this block's scores and stores
-        if (kb + 1 < nblk) gload_block<true, false, NT>(g, t, K, nullptr, t0 + kT, r);
-        f32x4 s[4];
-        score_block(lk, qf, s);
+    // The block of keys t0 .. t0 + 63; blocks come in order, and the first one starts at or
+    // before every row's first key.
+    __device__ __forceinline__ void store(float* __restrict__ S, float* patch, const f32x4 (&s)[4],
+                                          float scale, int t0, int qw, int w) const {
+        const int lane = threadIdx.x & 63, grp = lane >> 4, cc = lane & 15, nb = 2 * w + 1;
 #pragma unroll
         for (int ft = 0; ft < 4; ++ft)   // query lane%16, keys 16ft + 4grp .. +3
             *reinterpret_cast<f32x4*>(patch + (lane & 15) * kSLd + 4 + ft * 16 + 4 * grp) =
-                s[ft] * g.scale;
+                s[ft] * scale;
         wave_lds_order();
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
@@ -236,18 +216,51 @@ __global__ __launch_bounds__(64 * NW) void band_g2bmm_kernel(BandGeom g, int ntx
         patch[(lane >> 2) * kSLd + (lane & 3)] = patch[(lane >> 2) * kSLd + kT + (lane & 3)];
         wave_lds_order();
     }
-    // flush: the entries of the last block above its last stored chunk (lane -> row
-    // lane/4, entry lane%4 of the chunk after it)
-    const int rr = lane >> 2;
-    const int qq = qw + rr;
-    if (qq < t.lr) {
+    // The entries of the last block (keys from t0) above its last stored chunk (lane -> row
+    // lane/4, entry lane%4 of the chunk after it).
+    __device__ __forceinline__ void flush(const BandGeom& g, const Tile& t, float* __restrict__ S,
+                                          const float* patch, int t0, int qw, int w) const {
+        const int lane = threadIdx.x & 63, rr = lane >> 2, qq = qw + rr, nb = 2 * w + 1;
+        if (qq >= t.lr) return;
         const int64_t rb = row_index(g, t, qq) * nb;
-        const int js = t.q0 - w + (nblk - 1) * kT - qq + w;
-        const int64_t a = rb + js;
+        const int64_t a = rb + (t0 - qq + w);
         const int64_t x = (a & ~int64_t(3)) + kT + (lane & 3);
         const int j = (int)(x - rb);
         if (x < a + kT && j >= 0 && j < nb) S[x] = patch[rr * kSLd + 4 + (int)(x - a)];
     }
+};
+template <int NW>   // waves per workgroup: a tile of 16*NW queries
+__global__ __launch_bounds__(64 * NW) void band_g2bmm_kernel(BandGeom g, int ntx,
+                                                            const bf16_t* __restrict__ Q,
+                                                            const bf16_t* __restrict__ K,
+                                                            float* __restrict__ S) {
+    constexpr int NT = 64 * NW, FT = 16 * NW;
+    __shared__ u32x4 lk[kT * 8];
+    __shared__ __attribute__((aligned(16))) float ls[NW][16 * kSLd];
+    Tile t;
+    if (!tile_of<FT>(g, ntx, t)) return;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int qw = t.q0 + wv * 16;                  // the wave's first query
+    const int w = (int)g.w;
+    bf16x8 qf[2];
+    load_q_frags(g, t, Q, qw + (lane & 15), qf);
+    const int nblk = n_key_blocks<FT>(g);
+    SRows rows;
+    rows.init(g, t, qw);
+    KVRegs r;
+    gload_block<true, false, NT>(g, t, K, nullptr, t.q0 - w, r);
+    for (int kb = 0; kb < nblk; ++kb) {
+        const int t0 = t.q0 - w + kb * kT;
+        __syncthreads();
+        lstore_block<true, false, NT>(r, lk, nullptr);
+        __syncthreads();
+        // the next key block's loads overlap this block's scores and stores
+        if (kb + 1 < nblk) gload_block<true, false, NT>(g, t, K, nullptr, t0 + kT, r);
+        f32x4 s[4];
+        score_block(lk, qf, s);
+        rows.store(S, ls[wv], s, g.scale, t0, qw, w);
+    }
+    rows.flush(g, t, S, ls[wv], t.q0 - w + (nblk - 1) * kT, qw, w);
 }
 
 // ------------------------------------------------------------------- softmax
@@ -499,12 +512,16 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-template <typename OT, bool MASK, int kSlots, int NW, bool BUF, int HQ>
+// SOUT: the scores are also written to S [b][l][2w+1], in the G2BMM's way (aligned chunks
+// through a per-wave patch), before masks and softmax touch them.
+template <typename OT, bool MASK, int kSlots, int NW, bool BUF, int HQ, bool SOUT = false>
 __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(BandGeom g, int ntx,
                                                            const bf16_t* __restrict__ Q,
                                                            const bf16_t* __restrict__ K,
                                                            const bf16_t* __restrict__ V,
-                                                           OT* __restrict__ O) {
+                                                           OT* __restrict__ O,
+                                                           float* __restrict__ S) {
+    static_assert(!SOUT || HQ == 1, "the score patch holds 16 queries");
     // The reference moves only when a score exceeds it by more than kLazy (log2 units), so
     // p <= 2^kLazy: with at most 2w+1 terms per row, O and its normaliser stay far inside
     // the fp32 range, and bf16 p keeps its relative precision at any magnitude.  A wide
@@ -514,6 +531,7 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
     constexpr int kFT = NW * kQW;         // queries per tile (NW waves)
     constexpr int kPass = 64 / (NW * 8);  // copy instructions per lane per 64-row block
     __shared__ u32x4 lds[kSlots * kSlotChunks];
+    __shared__ __attribute__((aligned(16))) float ls[SOUT ? NW : 1][SOUT ? 16 * kSLd : 4];
     Tile t;
     {
         const int nblk_all = gridDim.x;
@@ -534,7 +552,9 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
     // scale * log2(e), kept >= the smallest normal float: with scale 0 every score then
     // maps to exp2(~0) = 1 exactly, and a masked score (-inf) still maps to 0
     const float sl2 = fmaxf(fabsf(g.scale) * 1.4426950408889634f, 1.17549435e-38f);
-    const uint32_t qflip = g.scale < 0.f ? 0x80008000u : 0u;
+    // (SOUT needs the scores of Q itself and negates them after their store: the MFMA's sum of
+    // negated products can differ in the last bit)
+    const uint32_t qflip = !SOUT && g.scale < 0.f ? 0x80008000u : 0u;
 
     bf16x8 qf[HQ][2];
 #pragma unroll
@@ -612,7 +632,8 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
     };
     // Iteration it handles key block (it - q0 / 64) mod nblk, so that the tiles that share a
     // block read it in the same iteration, while it is in L2 (90.5 -> 88.5 us)
-    const int first = (t.q0 / kT) % nblk;
+    // (SOUT carries scores from one block to the next and takes them in order)
+    const int first = SOUT ? 0 : (t.q0 / kT) % nblk;
     auto block_of = [&](int it) { const int x = it - first; return x < 0 ? x + nblk : x; };
     auto dma = [&](int it) { dma_block(it, block_of(it)); };
     // LDS byte offsets (within a slot) of this lane's fragment reads
@@ -685,6 +706,9 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
         return __any(n) != 0;
     };
 
+    SRows srow;
+    if constexpr (SOUT) srow.init(g, t, qa);
+
     // One block iteration: scores, softmax and P*V of block kb, which lies in slot `slot`.
     auto step = [&](int kb, auto slot, bool checked) {
         constexpr int kSlot = decltype(slot)::value;
@@ -694,6 +718,13 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
             bf16x8 kf[4][2];
             read_k(slot, kf);
             scores(kf, s);
+        }
+        if constexpr (SOUT) {
+            if (!checked) srow.store(S, ls[wv], s[0], g.scale, t0, qa, w);
+            if (g.scale < 0.f) {
+#pragma unroll
+                for (int ft = 0; ft < 4; ++ft) s[0][ft] = -s[0][ft];
+            }
         }
         // band (and range) mask, in place, on blocks that cross an edge: key c = 16ft + v of
         // the lane's 4grp-based run is inside from lower to upper (two instructions a score)
@@ -826,6 +857,7 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
             });
     };
     pass(false);
+    if constexpr (SOUT) srow.flush(g, t, S, ls[wv], t.q0 - w + hi * kT, qa, w);
     // A score more than ~127 log2 units above its row's reference made p, and with it the
     // denominator or O, infinite (so does an infinite or NaN input).  The tile is then
     // evaluated again with every score compared; the waves of the workgroup agree on it
@@ -1220,7 +1252,8 @@ hipError_t launch_fused_nw(const BandGeom& g, const void* q, const void* k, cons
     const bool buf = (l0 + g.w + 4 * kT) * g.dil * kD * 2 < (int64_t(1) << 31);
 #define OLLIE_FUSED(OT, M, B)                                                                \
     hipLaunchKernelGGL((band_fused_kernel<OT, M, 2, NW, B, HQ>), grid, dim3(64 * NW), 0, stream, \
-                       g, ntx, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (OT*)o)
+                       g, ntx, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (OT*)o, \
+                       (float*)nullptr)
 #define OLLIE_FUSED_B(OT, M)            \
     if (buf) OLLIE_FUSED(OT, M, true);  \
     else OLLIE_FUSED(OT, M, false)
@@ -1233,6 +1266,31 @@ hipError_t launch_fused_nw(const BandGeom& g, const void* q, const void* k, cons
     }
 #undef OLLIE_FUSED_B
 #undef OLLIE_FUSED
+    return hipGetLastError();
+}
+
+// Scores and O from one pass (S fp32 [b][l][2w+1]): the 16-query waves with the score store.
+hipError_t launch_band_scores(const BandGeom& g, const void* q, const void* k, const void* v,
+                              void* o, float* s, int o_bf16, int mask, hipStream_t stream) {
+    const int64_t l0 = (g.l + g.dil - 1) / g.dil;
+    const int ntx = (int)((l0 + 63) / 64);
+    const dim3 grid((unsigned)(ntx * g.dil * g.b));
+    const bool buf = (l0 + g.w + 4 * kT) * g.dil * kD * 2 < (int64_t(1) << 31);
+#define OLLIE_SCORES(OT, M, B)                                                                  \
+    hipLaunchKernelGGL((band_fused_kernel<OT, M, 2, 4, B, 1, true>), grid, dim3(256), 0, stream, \
+                       g, ntx, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (OT*)o, s)
+#define OLLIE_SCORES_B(OT, M)            \
+    if (buf) OLLIE_SCORES(OT, M, true);  \
+    else OLLIE_SCORES(OT, M, false)
+    if (o_bf16) {
+        if (mask) OLLIE_SCORES_B(bf16_t, true);
+        else OLLIE_SCORES_B(bf16_t, false);
+    } else {
+        if (mask) OLLIE_SCORES_B(float, true);
+        else OLLIE_SCORES_B(float, false);
+    }
+#undef OLLIE_SCORES_B
+#undef OLLIE_SCORES
     return hipGetLastError();
 }
 

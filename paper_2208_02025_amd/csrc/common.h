@@ -220,6 +220,8 @@ hipError_t launch_band_softmax(const BandGeom& g, const float* s, void* p, int m
                                hipStream_t stream);
 hipError_t launch_band_gbmm(const BandGeom& g, const void* p, const void* v, void* o,
                             int o_bf16, hipStream_t stream);
+hipError_t launch_band_scores(const BandGeom& g, const void* q, const void* k, const void* v,
+                              void* o, float* s, int o_bf16, int mask, hipStream_t stream);
 hipError_t launch_band_fused(const BandGeom& g, const void* q, const void* k, const void* v,
                              void* o, int o_bf16, int mask, int shape, hipStream_t stream);
 

@@ -72,3 +72,23 @@ def test_nonfinite_query_stays_local(b):
     ref = torch.zeros_like(bad)
     ref[0, 100] = True
     assert torch.equal(bad, ref)
+
+
+@pytest.mark.parametrize("b,l,w,dil", CASES[:9] + [(2, 200, 2, 1), (1, 1200, 511, 1), (40, 300, 33, 2)])
+@pytest.mark.parametrize("mask,scale", [(False, 0.125), (True, 1.0), (False, -0.5)])
+def test_scores_with_o(b, l, w, dil, mask, scale):
+    """One kernel for S and O: S has the G2BMM stage's bits (and nothing around it is
+    written), O agrees with the three stages."""
+    import paper_2208_02025_amd as ol
+    g = torch.Generator().manual_seed(l)
+    q, k, v = (torch.randn(b, l, 64, generator=g).bfloat16().cuda() for _ in range(3))
+    nb = 2 * w + 1
+    n = b * l * nb
+    guard = torch.full((n + 128,), 7.0, device="cuda")
+    s = guard[64:64 + n].view(b, l, nb)
+    o = torch.full((b, l, 64), float("nan"), device="cuda")
+    ol.banded_bmm(q, k, v, w, dil, scale, mask_invalid=mask, return_s=True, out=o, s_out=s)
+    assert torch.equal(s, ol.band_g2bmm(q, k, w, dil, scale))
+    assert (guard[:64] == 7).all() and (guard[64 + n:] == 7).all()
+    ref = ol.banded_bmm(q, k, v, w, dil, scale, mask_invalid=mask, staged=True)
+    assert (o - ref).abs().max() <= 2.0 ** -7 * v.float().abs().max()
