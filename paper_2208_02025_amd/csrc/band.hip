@@ -632,8 +632,9 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
     };
     // Iteration it handles key block (it - q0 / 64) mod nblk, so that the tiles that share a
     // block read it in the same iteration, while it is in L2 (90.5 -> 88.5 us)
-    // (SOUT carries scores from one block to the next and takes them in order)
-    const int first = SOUT ? 0 : (t.q0 / kT) % nblk;
+    // (SOUT carries scores from one block to the next and takes them in order; with two
+    // blocks the order gained nothing: b 74 l 900 w 14 dil 3 13.2 us, 12.5 in order)
+    const int first = SOUT || nblk <= 2 ? 0 : (t.q0 / kT) % nblk;
     auto block_of = [&](int it) { const int x = it - first; return x < 0 ? x + nblk : x; };
     auto dma = [&](int it) { dma_block(it, block_of(it)); };
     // LDS byte offsets (within a slot) of this lane's fragment reads
@@ -696,6 +697,8 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
             }
     };
 
+    // few blocks: comparing every score costs less than the check at the end and its barrier
+    const bool always = nblk <= 4;
     // Whether a query of the wave has no reference yet (its reference is -inf)
     bool unset = true;
     auto no_reference = [&]() {
@@ -720,7 +723,7 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
             scores(kf, s);
         }
         if constexpr (SOUT) {
-            if (!checked) srow.store(S, ls[wv], s[0], g.scale, t0, qa, w);
+            if (!checked || always) srow.store(S, ls[wv], s[0], g.scale, t0, qa, w);
             if (g.scale < 0.f) {
 #pragma unroll
                 for (int ft = 0; ft < 4; ++ft) s[0][ft] = -s[0][ft];
@@ -856,13 +859,13 @@ __global__ __launch_bounds__(64 * NW, HQ <= 2 ? 4 : 2) void band_fused_kernel(Ba
                     iterate(it + decltype(slot)::value, slot, checked);
             });
     };
-    pass(false);
+    pass(always);
     if constexpr (SOUT) srow.flush(g, t, S, ls[wv], t.q0 - w + hi * kT, qa, w);
     // A score more than ~127 log2 units above its row's reference made p, and with it the
     // denominator or O, infinite (so does an infinite or NaN input).  The tile is then
     // evaluated again with every score compared; the waves of the workgroup agree on it
     // through the idle ring.
-    {
+    if (!always) {
         float bad = 0.f;
 #pragma unroll
         for (int hq = 0; hq < HQ; ++hq) {
