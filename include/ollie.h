@@ -70,7 +70,8 @@ typedef enum {
  *   OLLIE_FUSED_TILE(n), n in 0..14: tile shape of the fused GEMM + eOperator kernel
  *     (conv entry points; ignored when the call takes the two-stage path).
  *   OLLIE_GEMM_TILE(n), n in 0..4: tile shape of the GEMM stage kernel (conv entry
- *     points on the two-stage path; ignored on the fused path).
+ *     points on the two-stage path, which an fp32 call that names one keeps to; ignored on
+ *     the fused path).
  *   OLLIE_BAND_SHAPE(n), n in 0..3: wave shape of the fused band kernel (banded_bmm
  *     without OLLIE_BAND_STAGED).
  * An n outside its range gives OLLIE_EINVAL. */
@@ -182,7 +183,8 @@ const char* ollie_version(void);
  *   out[n][ho][wo][k] = sum_{r,s} [0 <= hi < h][0 <= wi < w] Y[(n*h+hi)*w+wi][(r*S+s)*K+k]
  *   with hi = ho*stride_h - pad_h + r, wi = wo*stride_w - pad_w + s.
  * x: X, wt: Wt, out: out (layouts above).  ws: workspace of at least
- * ollie_conv_workspace_bytes(desc, 0, flags) bytes (holds Y).  flags: OLLIE_Y_BF16,
+ * ollie_conv_workspace_bytes(desc, 0, flags) bytes (holds Y; an fp32 call may keep Y in
+ * registers instead, with the same results, and leaves ws as it is).  flags: OLLIE_Y_BF16,
  * OLLIE_FUSE_EPILOGUE.
  * Rejects dil != 1 (OLLIE_EINVAL; use derived_dilated_conv2d).
  *

@@ -24,7 +24,7 @@ LIB = os.path.join(HERE, "libollie.so")
 STAMP = LIB + ".sha256"
 HEADER = os.path.join(os.path.dirname(HERE), "include", "ollie.h")
 SOURCES = ["abi.hip", "gemm.hip", "eop.hip", "band.hip", "conv_fused.hip", "conv_cols.hip",
-           "split3.hip"]
+           "conv_f32.hip", "split3.hip"]
 ARCH = "gfx950"
 
 # Packed fp32 ops are disabled for all device code (the host pass warns that it does
@@ -47,7 +47,8 @@ def _hipcc() -> str:
 # keeps them in place (with accumulators in AGPRs the register allocator shuffled them
 # between the two register files every iteration).
 SOURCE_FLAGS = {"conv_fused.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-                "conv_cols.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+                "conv_cols.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+                "conv_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def source_digest(csrc: str = CSRC, header: str = HEADER) -> str:

@@ -375,8 +375,15 @@ int conv_common(const ollie_conv_desc* d, int transposed, const void* x, const v
     if (dry) return OLLIE_OK;
     hipStream_t s = (hipStream_t)stream;
     const int y_bf16 = (flags & OLLIE_Y_BF16) ? 1 : 0;
-    hipError_t e = launch_gemm_nt(m, nc, d->c, x, wt, ws, d->in_dtype == OLLIE_BF16, y_bf16,
-                                  gemm_tile(flags), s);
+    hipError_t e;
+    // an automatic fp32 forward call with an fp32 scope: the same sums without Y in memory
+    if (d->in_dtype == OLLIE_F32 && !transposed && !y_bf16 && gemm_tile(flags) < 0 &&
+        launch_conv_f32(conv_geom(d, ho, wo), x, wt, out, d->out_dtype == OLLIE_BF16, epi, s, e)) {
+        if (e != hipSuccess) return hip_fail(e, "fp32 convolution launch");
+        return OLLIE_OK;
+    }
+    e = launch_gemm_nt(m, nc, d->c, x, wt, ws, d->in_dtype == OLLIE_BF16, y_bf16,
+                       gemm_tile(flags), s);
     if (e != hipSuccess) return hip_fail(e, "GEMM stage launch");
     e = launch_eop_gather(conv_geom(d, ho, wo), transposed, ws, y_bf16, out,
                           d->out_dtype == OLLIE_BF16, epi, s);

@@ -186,6 +186,11 @@ struct ConvGeom {
 hipError_t launch_eop_gather(const ConvGeom& g, int transposed, const void* y, int y_bf16,
                              void* out, int out_bf16, const Epi& epi, hipStream_t stream);
 
+// The fp32 convolution (forward form) as one kernel with the two stages' bits; false where the
+// two stages stay.
+bool launch_conv_f32(const ConvGeom& g, const void* x, const void* wt, void* out, int out_bf16,
+                     const Epi& epi, hipStream_t stream, hipError_t& err);
+
 // The R x S -> 3x3 derived form's two eOperators (the 3x3 stage's OffsetAdd and the
 // block OffsetAdd) fused into one OffsetAdd over the split form's scope
 // Y [n*h*w][9*ceil(R/3)*ceil(S/3)*K] (g: the original stride-1 convolution).

@@ -1,0 +1,262 @@
+// fp32 convolution in one kernel: the two-stage expression (GEMM into the instantiated scope
+// Y, then OffsetAdd) with Y kept in registers.  Each tap's product is summed over the channels
+// in the order and with the instructions of gemm_nt_f32_dma_kernel, and the taps that lie in
+// the image are added in the eOperator's order, so every output has the two-stage path's bits.
+//
+// A tile is BM output pixels x BN output channels; its contraction runs over (tap, 32-channel
+// k-tile) steps.  Operand rows of 128 bytes reach LDS by direct copies through a ring of NSTAGE
+// k-tiles with the GEMM's chunk swizzle: A rows gathered from X per tap (a pixel outside the
+// image, and channels past C, get an offset past the buffer and read zeros), B rows from Wt.
+// VEC = 4 copies 16-byte chunks (C % 4 == 0), VEC = 1 single floats.  Operands under 2 GiB.
+//
+// Measured (us, two stages / this kernel, launches back to back in a graph):
+//   8x56x56 64->64 3x3 36.7 / 28.6, 8x64x64 3->64 3x3 36.5 / 22.9, 8x56x56 64->128 1x1
+//   19.8 / 10.4 (64x64 tiles); 4x28x28 64->64 3x3 10.8 / 9.8, 7x61x21 18->57 3x3 stride 2
+//   19.4 / 9.3, 2x32x32 100->50 1x1 8.0 / 4.1 (32x32 tiles).
+// What bounds it: a wave's step is serial (barrier, LDS reads, a chain of fp32 MFMAs), 0.75 us
+// for 1024 MFMA cycles of a 64x64 tile, whatever the depth of the copy ring.
+#include "common.h"
+
+namespace ollie {
+
+namespace {
+
+struct F32Conv {
+    int M, C, H, W, K, R, S, ho, wo, sh, sw, ph, pw, dh, dw;
+    int x_bytes, w_bytes, vec_out;
+};
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int MINB, int VEC, typename OT>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, MINB)
+void conv_f32_kernel(const float* __restrict__ X, const float* __restrict__ Wt,
+                     OT* __restrict__ out, F32Conv P, int tiles_n, Epi epi) {
+    constexpr int NW = WAVES_M * WAVES_N, BKF = 32;
+    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
+    constexpr int FM = WM / 16, FN = WN / 16;
+    constexpr int STAGE_CHUNKS = (BM + BN) * 8;           // A rows, then B rows
+    constexpr int LANES = 32 / VEC;                       // lanes per row of one copy
+    constexpr int RPI = 64 / LANES;                       // rows per wave-wide copy
+    constexpr int RSTEP = RPI * NW;                       // rows between a wave's copies
+    constexpr int A_LOADS = BM / RSTEP, B_LOADS = BN / RSTEP;
+    constexpr int LOADS = A_LOADS + B_LOADS;
+    static_assert(BM % RSTEP == 0 && BN % RSTEP == 0 && RSTEP % 8 == 0, "whole wave copies");
+    static_assert((NSTAGE - 1) * LOADS < 64, "vmcnt range");
+    __shared__ u32x4 lds[NSTAGE * STAGE_CHUNKS];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int nblk = gridDim.x, bid = blockIdx.x;
+    const int id = (nblk & 7) == 0 ? (bid & 7) * (nblk >> 3) + (bid >> 3) : bid;
+    const int tm = id / tiles_n;
+    const int m0 = tm * BM, n0 = (id - tm * tiles_n) * BN;
+
+    // input row and column of output pixel m under tap (0, 0); past the last pixel a row that
+    // no tap brings into the image
+    auto origin = [&](int m, int& n, int& hi, int& wi) {
+        const int q = m / P.wo, ow = m - q * P.wo;
+        n = q / P.ho;
+        hi = m < P.M ? (q - n * P.ho) * P.sh - P.ph : -(1 << 30);
+        wi = ow * P.sw - P.pw;
+    };
+    // this lane's place in a copy: row lrow (the same modulo 8 in every copy), k offset lk
+    const int lrow = wave * RPI + lane / LANES;
+    const int lpos = (lane % LANES) * VEC;
+    const int lk = (((lpos >> 2) ^ (lrow & 7)) << 2) + (lpos & 3);
+    uint32_t aoff[A_LOADS];
+    int ah[A_LOADS], aw[A_LOADS];
+#pragma unroll
+    for (int i = 0; i < A_LOADS; ++i) {
+        int n;
+        origin(m0 + i * RSTEP + lrow, n, ah[i], aw[i]);
+        // only valid taps use it, where the whole sum lies in [0, 2^31)
+        aoff[i] = (((uint32_t)n * P.H + (uint32_t)ah[i]) * P.W + (uint32_t)aw[i]) * P.C * 4u + lk * 4u;
+    }
+    const uint32_t boff = ((uint32_t)(n0 + lrow) * P.C + lk) * 4u;
+    const uint32_t rowc = (uint32_t)P.C * 4u;
+    const int ktiles = (P.C + BKF - 1) / BKF, steps = P.R * P.S * ktiles;
+
+    int ir = 0, is = 0, ik = 0;                           // tap and k-tile of the next copies
+    auto issue = [&](int buf) {
+        const bool kin = ik * BKF + lk < P.C;
+        const int dh = ir * P.dh, dw = is * P.dw;
+        const uint32_t add = ((uint32_t)dh * (uint32_t)P.W + (uint32_t)dw) * rowc + ik * (BKF * 4);
+        const uint32_t tap = (uint32_t)(ir * P.S + is) * P.K * rowc + ik * (BKF * 4);
+        u32x4* dst = lds + buf * STAGE_CHUNKS;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const bool is_a = i < A_LOADS;
+            const int r = is_a ? i : i - A_LOADS;
+            uint32_t off;
+            if (is_a) {
+                const bool ok = kin && (unsigned)(ah[r] + dh) < (unsigned)P.H &&
+                                (unsigned)(aw[r] + dw) < (unsigned)P.W;
+                off = ok ? aoff[r] + add : 0x80000000u;
+            } else {
+                // rows past K belong to columns that are not stored
+                off = kin && n0 + r * RSTEP + lrow < P.K ? boff + r * RSTEP * rowc + tap
+                                                         : 0x80000000u;
+            }
+            lds_void* to = (lds_void*)(dst + ((is_a ? 0 : BM) + r * RSTEP + wave * RPI) * 8);
+            if constexpr (VEC == 4)
+                buffer_copy16(is_a ? X : Wt, is_a ? P.x_bytes : P.w_bytes, off, 0, to);
+            else
+                buffer_copy4(is_a ? X : Wt, is_a ? P.x_bytes : P.w_bytes, off, 0, to);
+        }
+        if (++ik == ktiles) {
+            ik = 0;
+            if (++is == P.S) {
+                is = 0;
+                ++ir;
+            }
+        }
+    };
+
+    // the pixels whose sums this lane holds
+    int ph[FM], pw[FM];
+#pragma unroll
+    for (int j = 0; j < FM; ++j) {
+        int n;
+        origin(m0 + wm * WM + j * 16 + (lane & 15), n, ph[j], pw[j]);
+    }
+    f32x4 acc[FN][FM], tot[FN][FM];
+#pragma unroll
+    for (int i = 0; i < FN; ++i)
+#pragma unroll
+        for (int j = 0; j < FM; ++j) acc[i][j] = tot[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+#pragma unroll
+    for (int s = 0; s < NSTAGE - 1; ++s)
+        if (s < steps) issue(s);
+    int buf = 0, nbuf = NSTAGE - 1, cr = 0, cs = 0, ck = 0;
+    for (int t = 0; t < steps; ++t) {
+        if (t + NSTAGE - 2 < steps) wait_vmcnt<(NSTAGE - 2) * LOADS>();
+        else wait_vmcnt<0>();
+        block_barrier();
+        if (t + NSTAGE - 1 < steps) issue(nbuf);
+        const f32x4* la = reinterpret_cast<const f32x4*>(lds + buf * STAGE_CHUNKS);
+        const f32x4* lb = la + BM * 8;
+#pragma unroll
+        for (int kk = 0; kk < BKF / 16; ++kk) {
+            const int ch = kk * 4 + (lane >> 4);
+            f32x4 fa[FN], fb[FM];
+#pragma unroll
+            for (int i = 0; i < FN; ++i) fa[i] = lb[tile_swz(wn * WN + i * 16 + (lane & 15), ch)];
+#pragma unroll
+            for (int j = 0; j < FM; ++j) fb[j] = la[tile_swz(wm * WM + j * 16 + (lane & 15), ch)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < FN; ++i)
+#pragma unroll
+                    for (int j = 0; j < FM; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][e], fb[j][e],
+                                                                         acc[i][j], 0, 0, 0);
+        }
+        buf = buf + 1 == NSTAGE ? 0 : buf + 1;
+        nbuf = nbuf + 1 == NSTAGE ? 0 : nbuf + 1;
+        if (++ck == ktiles) {                             // the tap's sum is complete
+            ck = 0;
+#pragma unroll
+            for (int j = 0; j < FM; ++j) {
+                const bool ok = (unsigned)(ph[j] + cr * P.dh) < (unsigned)P.H &&
+                                (unsigned)(pw[j] + cs * P.dw) < (unsigned)P.W;
+#pragma unroll
+                for (int i = 0; i < FN; ++i) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)           // (a zero row times inf is NaN)
+                        tot[i][j][v] = ok ? tot[i][j][v] + acc[i][j][v] : tot[i][j][v];
+                    acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                }
+            }
+            if (++cs == P.S) {
+                cs = 0;
+                ++cr;
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < FM; ++j) {
+        const int m = m0 + wm * WM + j * 16 + (lane & 15);
+        if (m >= P.M) continue;
+#pragma unroll
+        for (int i = 0; i < FN; ++i) {
+            const int k = n0 + wn * WN + i * 16 + 4 * (lane >> 4);
+            const int64_t o = (int64_t)m * P.K + k;
+            if (P.vec_out && k + 3 < P.K) {
+                Out<OT>::put4(out + o, epi_apply4(epi, tot[i][j], o, k));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (k + e < P.K) Out<OT>::put(out + o + e, epi_apply(epi, tot[i][j][e], o + e, k + e));
+            }
+        }
+    }
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTAGE, int MINB, typename OT>
+hipError_t go(const F32Conv& P, const void* x, const void* wt, void* out, const Epi& epi,
+              hipStream_t st) {
+    const int tn = (P.K + BN - 1) / BN, tm = (P.M + BM - 1) / BM;
+    const dim3 grid((unsigned)tm * tn), block(64 * WAVES_M * WAVES_N);
+    if (P.C % 4 == 0)
+        hipLaunchKernelGGL((conv_f32_kernel<BM, BN, WAVES_M, WAVES_N, NSTAGE, MINB, 4, OT>), grid,
+                           block, 0, st, (const float*)x, (const float*)wt, (OT*)out, P, tn, epi);
+    else
+        hipLaunchKernelGGL((conv_f32_kernel<BM, BN, WAVES_M, WAVES_N, NSTAGE, MINB, 1, OT>), grid,
+                           block, 0, st, (const float*)x, (const float*)wt, (OT*)out, P, tn, epi);
+    return hipGetLastError();
+}
+
+// Estimated times (us), fitted to 40 layers (1 to 8 images, 3 to 128 channels, 1x1 to 5x5,
+// strides 1 and 2).  A step of a 64x64 tile takes 0.75 us (1.7 with single-float copies) times
+// the tiles per CU, one of a 32x32 tile 0.38 (0.7), or 0.28 (0.45) a tile where several share a
+// CU; deeper copy rings gained nothing.  The two stages: 5.2 us of launches, the GEMM's products
+// at 110 TFLOP/s or the store of Y, 0.45 us a k-tile, the read of Y, and 0.3 us a tap in the
+// eOperator's tap loop (more than 3x3 taps).
+struct Times {
+    double t64, t32, staged;
+};
+Times estimate(const ConvGeom& g) {
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const int64_t m = g.n * g.ho * g.wo, kt = up(g.c, 32);
+    const double taps = (double)(g.r * g.s), steps = taps * kt;
+    const bool vec = g.c % 4 == 0;
+    const double per64 = (double)up(up(m, 64) * up(g.k, 64), 256);
+    const double per32 = (double)up(up(m, 32) * up(g.k, 32), 256);
+    const double lat = vec ? 0.38 : 0.7, thr = (vec ? 0.28 : 0.45) * per32;
+    const int64_t mi = g.n * g.h * g.w, nc = g.r * g.s * g.k;
+    const double y = 4.0 * mi * nc * 1e-6;               // MB
+    const double mm = 2.0 * up(mi, 64) * 64 * up(nc, 64) * 64 * kt * 32 / 110e6, st = y / 6.0;
+    return {2.6 + steps * (vec ? 0.75 : 1.7) * per64, 2.9 + steps * (lat > thr ? lat : thr),
+            5.2 + (mm > st ? mm : st) + 0.45 * kt + y / 5.0 + (taps > 9 ? 0.3 * taps : 0.0)};
+}
+
+}  // namespace
+
+bool launch_conv_f32(const ConvGeom& g, const void* x, const void* wt, void* out, int out_bf16,
+                     const Epi& epi, hipStream_t st, hipError_t& err) {
+    const int64_t lim = int64_t(1) << 31, m = g.n * g.ho * g.wo;
+    if (g.n * g.h * g.w * g.c * 4 >= lim || g.r * g.s * g.k * g.c * 4 >= lim || m * g.k >= lim)
+        return false;
+    // taps and pixels in 32-bit arithmetic
+    if (g.r * g.dh + g.ph + g.ho * g.sh >= lim / 4 || g.s * g.dw + g.pw + g.wo * g.sw >= lim / 4)
+        return false;
+    F32Conv P{(int)m, (int)g.c, (int)g.h, (int)g.w, (int)g.k, (int)g.r, (int)g.s, (int)g.ho,
+              (int)g.wo, g.sh, g.sw, g.ph, g.pw, g.dh, g.dw, (int)(g.n * g.h * g.w * g.c * 4),
+              (int)(g.r * g.s * g.k * g.c * 4), g.k % 4 == 0};
+    // Within 1 us the single launch wins: it saves the host 2-3 us.  A few long contractions
+    // (3x3 over 128 channels on 196 pixels: 16 us here, 7.8 in two stages) stay with the stages,
+    // whose GEMM spreads the taps over the chip.
+    const Times e = estimate(g);
+    if ((e.t64 < e.t32 ? e.t64 : e.t32) > e.staged + 1.0) return false;
+    if (e.t64 < e.t32)
+        err = out_bf16 ? go<64, 64, 4, 1, 2, 4, bf16_t>(P, x, wt, out, epi, st)
+                       : go<64, 64, 4, 1, 2, 4, float>(P, x, wt, out, epi, st);
+    else
+        err = out_bf16 ? go<32, 32, 2, 2, 4, 4, bf16_t>(P, x, wt, out, epi, st)
+                       : go<32, 32, 2, 2, 4, 4, float>(P, x, wt, out, epi, st);
+    return true;
+}
+
+}  // namespace ollie
